@@ -137,10 +137,17 @@ struct Run {
     part_off = L.part;
   }
 
+  // step (node index) at which node v's forward launch runs: its own, or,
+  // for a conv whose epilogue computes a residual add before the add's other
+  // input exists, the add's
+  int fwd_step(int v) const {
+    const int c = F.fwd[v];
+    return c && v < std::max(P.nodes[c].in0, P.nodes[c].in1) ? c : v;
+  }
   // last step (node index) of a band that reads node v's window
   int last_reader(int v) const {
     int c = v;
-    for (int k : P.cons[v]) c = std::max(c, k);
+    for (int k : P.cons[v]) c = std::max(c, fwd_step(k));
     return c;
   }
   // the windows node v's step writes (its own, and the residual add's when
@@ -347,18 +354,23 @@ struct Run {
       // (not with lifetime-packed forward windows: the add's window may
       // still belong to another node while the conv runs)
       const bool can_fuse = !packed;
-      const int fa = can_fuse ? F.fwd[v] : 0;
       const lrcnn_node &nd = P.nodes[v];
-      if (fa) {
-        // this conv's epilogue computes the residual add fa (its only
-        // consumer): output into the add's view, with the add's mask
+      // the add whose input v this step computes together with it (u: that
+      // input, v itself or, at the add's own step, a deferred one)
+      int u = can_fuse && F.fwd[v] ? v : 0;
+      if (can_fuse && nd.op == LRCNN_OP_ADD)
+        u = F.fwd[nd.in0] == v ? nd.in0 : F.fwd[nd.in1] == v ? nd.in1 : 0;
+      if (u && fwd_step(u) != v) {
+        // computed at the other of the two steps
+      } else if (u) {
+        // u's epilogue computes the residual add fa (its only consumer):
+        // output into the add's view, with the add's mask
+        const int fa = F.fwd[u];
         const lrcnn_node &an = P.nodes[fa];
-        const View other = act[an.in0 == v ? an.in1 : an.in0];
+        const View other = act[an.in0 == u ? an.in1 : an.in0];
         uint8_t *amk = mask_out ? (uint8_t *)mask_out[fa] : nullptr;
-        if ((st = node_fwd(v, q.a, q.b, act[fa], am, amk, &other, an.relu)) != LRCNN_OK)
+        if ((st = node_fwd(u, q.a, q.b, act[fa], nullptr, amk, &other, an.relu)) != LRCNN_OK)
           return st;
-      } else if (can_fuse && nd.op == LRCNN_OP_ADD && F.fwd[std::max(nd.in0, nd.in1)] == v) {
-        // computed with its later input
       } else {
         uint8_t *mk = mask_out ? (uint8_t *)mask_out[v] : nullptr;
         if ((st = node_fwd(v, q.a, q.b, dst, am, mk)) != LRCNN_OK) return st;
@@ -471,8 +483,9 @@ struct Run {
   }
 
   // The backward launch of v (a conv's input gradient, a max-pool's
-  // backward) initializes u's error window itself (no zeroing pass) when it
-  // writes every row of the window this band uses.
+  // backward) initializes u's error window itself (no zeroing pass) when its
+  // rows are the window's, or nearly (bwd_covers): it then runs over every
+  // row of the window this band uses.
   bool init_by_dgrad(int r, int v, int u, bool want_dx) const {
     const lrcnn_node &d = P.nodes[v];
     if (u == 0 && !want_dx) return false;
@@ -489,7 +502,7 @@ struct Run {
     if (qv.b <= qv.a) return false;
     const int y0 = std::max(0, qv.a * d.sh - d.ph);
     const int y1 = std::min(P.shp[u].h, (qv.b - 1) * d.sh - d.ph + d.kh);
-    return y0 == qu.lo && y1 == qu.hi;
+    return bwd_covers(y0, y1, qu.lo, qu.hi);
   }
 
   // Zero node u's error window for band r and bring in the error carried
@@ -548,8 +561,8 @@ struct Run {
         if (!holds(cv, q.lo, q.a)) return lrcnn_fail(LRCNN_EINVAL, "internal: carry rows not held");
       }
       if (fused(v)) {
-        // the add's backward already wrote this conv's error operand
-        if (carries) return lrcnn_fail(LRCNN_EINVAL, "internal: fused conv carries rows");
+        // the add's backward already wrote this conv's error operand and the
+        // rows it carries
       } else if (act_done[v]) {
         // the consumer's input gradient formed the error operand and carry
         act_done[v] = 0;
@@ -618,6 +631,9 @@ struct Run {
         c.part_bytes = L.part_bytes;
         if (dinit[u]) {
           // this launch writes every row of u's window: no zeroing pass
+          const Rows qu = band_rows(r, u);
+          c.y0 = qu.lo;
+          c.y1 = qu.hi;
           c.dst_init = 1;
           if (dinit_carry[u]) {
             if (!holds(dinit_cv[u], dinit_t[u], band_rows(r, u).b))
@@ -651,6 +667,9 @@ struct Run {
       int stage_a = 0;
       if (dinit[u]) {
         // this launch writes every row of u's window: no zeroing pass
+        const Rows qu = band_rows(r, u);
+        p.ua = qu.lo;
+        p.ub = qu.hi;
         p.dst_init = 1;
         if (dinit_carry[u]) {
           if (!holds(dinit_cv[u], dinit_t[u], band_rows(r, u).b))
@@ -669,10 +688,41 @@ struct Run {
       for (int k = 0; k < 2; ++k) {
         const int x = in_ids[k];
         AddSide &sd = side_in[k];
-        sd = AddSide{dlt[x], nullptr, nullptr, sv.c, 0, View{}, 0, 0};
-        if (dinit[x]) {
+        sd = AddSide{};
+        sd.win = dlt[x];
+        // nobody reads the input's error
+        sd.skip = x == 0 && !want_dx;
+        const Rows qx = band_rows(r, x);
+        if (fused(x)) {
+          // x's whole error for the band: the add's rows, and past them what
+          // the band below carried in; rows below x's own leave to the band
+          // above
+          const int t = sched == S_CARRY && r + 1 < P.nb ? P.tail[r][x] : qx.b;
+          if (qx.lo != a || qx.b < b || qx.hi != qx.b || (t != b && t < qx.b))
+            return lrcnn_fail(LRCNN_EINVAL, "internal: fused conv rows differ from the add's");
+          sd.eo.fact = 1;
+          sd.eo.fa = qx.a;
+          sd.eo.dc = View{ws + L.dc[x], (long long)(qx.b - qx.a) * sv.w * sv.c, qx.a, sv.w, sv.c,
+                          qx.b - qx.a};
+          sd.eo.scale = P.nodes[x].affine ? sc[x] : nullptr;
+          sd.init_hi = qx.b;
+          if (qx.b > b) {
+            sd.cinit = View{carry_ptr(x, r + 1), (long long)L.carry_cap[x] * sv.w * sv.c, b, sv.w,
+                            sv.c, L.carry_cap[x]};
+            sd.cinit_t = b;
+            if (t != b || !holds(sd.cinit, b, qx.b))
+              return lrcnn_fail(LRCNN_EINVAL, "internal: carry rows not held");
+          }
+          if (qx.a > qx.lo) {
+            if (sched != S_CARRY || r == 0 || !L.carry2[x])
+              return lrcnn_fail(LRCNN_EINVAL, "internal: fused conv carries rows");
+            sd.eo.carry = View{carry_ptr(x, r), (long long)L.carry_cap[x] * sv.w * sv.c, qx.lo,
+                               sv.w, sv.c, L.carry_cap[x]};
+            if (!holds(sd.eo.carry, qx.lo, qx.a))
+              return lrcnn_fail(LRCNN_EINVAL, "internal: carry rows not held");
+          }
+        } else if (dinit[x]) {
           // this launch writes every row of x's window: no zeroing pass
-          const Rows qx = band_rows(r, x);
           sd.init = 1;
           sd.init_hi = qx.hi;
           if (dinit_carry[x]) {
@@ -682,14 +732,6 @@ struct Run {
             sd.cinit_t = dinit_t[x];
           }
           dinit[x] = 0;
-        }
-        if (fused(x)) {
-          // own rows of the conv input equal the add's rows (1 x 1 window)
-          const Rows qx = band_rows(r, x);
-          if (qx.a != a || qx.b != b)
-            return lrcnn_fail(LRCNN_EINVAL, "internal: fused conv rows differ from the add's");
-          sd.dc = ws + L.dc[x];
-          sd.scale = P.nodes[x].affine ? sc[x] : nullptr;
         }
       }
       LAUNCH(launch_add_bwd(dt, dlt[v], act[v], side_in[0], side_in[1], d.relu, B, a, b, sv.w,
@@ -709,15 +751,14 @@ struct Run {
     const int n = P.n, B = P.cfg.batch;
     const bool want_dx = dx != nullptr;
     std::fill(act_done.begin(), act_done.end(), 0);
-    // seed: the band's own rows of dL/dy
+    // the last node's error is dL/dy, read in place (no consumer adds to it
+    // and no band carries rows of it)
     {
       const Rows q = band_rows(r, n - 1);
-      int st = init_delta(r, n - 1);
-      if (st != LRCNN_OK) return st;
-      const Shape &s = P.shp[n - 1];
-      LAUNCH(launch_rows_copy(P.dy_f32 ? DT_F32 : dt, DT_F32, full(const_cast<void *>(dy), n - 1),
-                              dlt[n - 1], 0, B, q.a, q.b, s.w, s.c, stream),
-             "seed error");
+      if (q.lo != q.a || q.hi != q.b)
+        return lrcnn_fail(LRCNN_EINVAL, "internal: shared rows of the output node");
+      dlt[n - 1] = full(const_cast<void *>(dy), n - 1);
+      dlt[n - 1].st = P.dy_f32 ? 0 : 1;
     }
     for (int v = n - 1; v >= 1; --v) {
       const lrcnn_node &d = P.nodes[v];
@@ -730,7 +771,7 @@ struct Run {
       int ins[2] = {d.in0, d.op == LRCNN_OP_ADD ? d.in1 : -1};
       for (int u : ins)
         if (u >= 0 && first_consumer[u] == v && !fused(u)) {
-          if (u == 0 && !want_dx && P.nodes[v].op == LRCNN_OP_CONV) {
+          if (u == 0 && !want_dx && P.nodes[v].op != LRCNN_OP_MAXPOOL) {
             // nothing reads the input's error: only its view is needed
             View cv;
             int t = 0;
@@ -763,7 +804,7 @@ struct Run {
       // owns none of its rows (node_bwd then launches nothing)
       const Rows qv = band_rows(r, v);
       if (sched == S_CARRY && r > 0 && (d.op != LRCNN_OP_CONV || qv.b <= qv.a) &&
-          !act_done[v]) {
+          !act_done[v] && !fused(v)) {
         const Rows q = band_rows(r, v);
         if (q.a > q.lo) {
           const Shape &s = P.shp[v];

@@ -440,15 +440,49 @@ __device__ __forceinline__ void st4(bf16 *p, const float (&v)[4]) {
   q.y = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
   *(uint2 *)p = q;
 }
-template <typename T, int V>
-__device__ __forceinline__ void ldv(const T *p, float (&v)[4]) {
-  if (V == 4) ld4(p, v);
-  else v[0] = ldf(p);
+// V = 8, 4 or 1 consecutive elements (whole 16-byte accesses for V = 8,
+// one access for V = 4)
+template <typename T, int V, int N>
+__device__ __forceinline__ void ldv(const T *p, float (&v)[N]) {
+  static_assert(N >= V, "vector width");
+  if constexpr (V == 1) {
+    v[0] = ldf(p);
+  } else if constexpr (V == 8 && sizeof(T) == 2) {
+    const uint4 q = *(const uint4 *)p;
+    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(w[i] << 16);
+      v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; i += 4) {
+      float t[4];
+      ld4(p + i, t);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[i + k] = t[k];
+    }
+  }
 }
-template <typename T, int V>
-__device__ __forceinline__ void stv(T *p, const float (&v)[4]) {
-  if (V == 4) st4(p, v);
-  else stf(p, v[0]);
+template <typename T, int V, int N>
+__device__ __forceinline__ void stv(T *p, const float (&v)[N]) {
+  static_assert(N >= V, "vector width");
+  if constexpr (V == 1) {
+    stf(p, v[0]);
+  } else if constexpr (V == 8 && sizeof(T) == 2) {
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      w[i] = (uint32_t)f2bf(v[2 * i]) | ((uint32_t)f2bf(v[2 * i + 1]) << 16);
+    *(uint4 *)p = make_uint4(w[0], w[1], w[2], w[3]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; i += 4) {
+      const float t[4] = {v[i], v[i + 1], v[i + 2], v[i + 3]};
+      st4(p + i, t);
+    }
+  }
 }
 
 // Decompose a flat index over B x rows x (W*C/V) into (b, row, inner):
@@ -493,6 +527,15 @@ static RowIter row_iter(int B, int r0, int r1, int W, int C, int V) {
   for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total; \
        idx += (long long)gridDim.x * blockDim.x)
 
+// V values of an error a backward launch reads at (b, y, inner): a float32
+// window, or dL/dy in the storage dtype (v.st).
+template <typename T, int V, int N>
+__device__ __forceinline__ void ld_err(const View &v, int b, int y, int inner, float (&d)[N]) {
+  const long long o = view_off(v, b, y, inner);
+  if (v.st) ldv<T, V>((const T *)v.p + o, d);
+  else ldv<float, V>((const float *)v.p + o, d);
+}
+
 // Base value an input-gradient element is added to: the error window's
 // current value, or, when the launch initializes the window, the carried
 // error (rows >= cinit_t) or zero. `inner` = x * C + c.
@@ -513,9 +556,9 @@ __device__ __forceinline__ const float *dgrad_base(const ConvArgs &a, int b, int
 // (eo.fact), as the producer's error operand (ReLU mask, affine scale,
 // storage dtype; the same arithmetic as the activation backward) or its
 // float32 carry to the previous band.
-template <typename T, int V>
+template <typename T, int V, int N>
 __device__ __forceinline__ void err_out(const ErrOut &eo, int C, int b, int y, int x, int n,
-                                        float (&o)[4], float *d) {
+                                        float (&o)[N], float *d) {
   if (!eo.fact) {
     stv<float, V>(d, o);
     return;
@@ -526,7 +569,7 @@ __device__ __forceinline__ void err_out(const ErrOut &eo, int C, int b, int y, i
     return;
   }
   if (eo.relu) {
-    float zz[4];
+    float zz[N];
     ldv<T, V>((const T *)eo.z.p + view_off(eo.z, b, y, inner), zz);
 #pragma unroll
     for (int e = 0; e < V; ++e)

@@ -209,12 +209,34 @@ int launch_pool_fwd(int dt, const PoolArgs &a0, void *stream) {
   return (int)hipGetLastError();
 }
 
+// argmax bytes of V consecutive channels (V = 8 or 4: one access; the
+// launcher takes those widths only where the rows keep them aligned)
+template <int V>
+__device__ __forceinline__ void ld_arg(const uint8_t *p, uint32_t (&m)[V]) {
+  if constexpr (V == 1) {
+    m[0] = *p;
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; i += 4) {
+      const uint32_t w = *(const uint32_t *)(p + i);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) m[i + k] = (w >> (8 * k)) & 0xffu;
+    }
+  }
+}
+
+// HBM-bound: per producer element its share of the argmax bytes and the
+// consumer's error (read again from L2 by the neighbouring windows' pixels),
+// then the error operand (z read, storage dtype written) or the float32
+// window. Forming the operand here also in bands whose last producer row no
+// window reaches saves the window and a pass over it (the stem at 8 x 2400 x
+// 3600, 32 bands: 19.5 -> 14.9 ms per step).
 template <typename T, int V>
 __global__ void pool_bwd_kernel(PoolBwdArgs a) {
   const int Ru = a.ub - a.ua, R = a.y1 - a.y0;
   const int CV = a.C / V;
   const long long total = (long long)a.B * Ru * a.Wu * CV;
-  const long long vrow = (long long)a.Wv * a.C, urow = (long long)a.Wu * a.C;
+  const long long urow = (long long)a.Wu * a.C;
   const bool fast = total < (1ll << 32);
   GRID_STRIDE(idx, total) {
     int c, xi, yi, b;
@@ -237,21 +259,26 @@ __global__ void pool_bwd_kernel(PoolBwdArgs a) {
     const int yhi = min(a.y1 - 1, fdiv(yi + a.ph, a.sh));
     const int xlo = max(0, fdiv(xi + a.pw - a.kw, a.sw) + 1);
     const int xhi = min(a.Wv - 1, fdiv(xi + a.pw, a.sw));
-    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+    float sum[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) sum[e] = 0.f;
     for (int y = ylo; y <= yhi; ++y)
       for (int x = xlo; x <= xhi; ++x) {
-        const int tp = (yi - (y * a.sh - a.ph)) * a.kw + (xi - (x * a.sw - a.pw));
+        const uint32_t tp = (yi - (y * a.sh - a.ph)) * a.kw + (xi - (x * a.sw - a.pw));
         const long long ai = (((long long)b * R + (y - a.y0)) * a.Wv + x) * a.C + c;
-        float dv[4];
-        ldv<float, V>((const float *)a.dv.p + b * a.dv.bs + (y - a.dv.row0) * vrow +
-                          (long long)x * a.C + c, dv);
+        float dv[V];
+        uint32_t m[V];
+        ld_err<T, V>(a.dv, b, y, x * a.C + c, dv);
+        ld_arg<V>(a.am + ai, m);
 #pragma unroll
         for (int e = 0; e < V; ++e)
-          if (a.am[ai + e] == tp) sum[e] += dv[e];
+          if (m[e] == tp) sum[e] += dv[e];
       }
     float *d = (float *)a.du.p + b * a.du.bs + (yi - a.du.row0) * urow + (long long)xi * a.C + c;
     const float *bp = err_base(a.dst_init, a.cinit, a.cinit_t, b, yi, (long long)xi * a.C + c, d);
-    float q[4] = {0.f, 0.f, 0.f, 0.f};
+    float q[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) q[e] = 0.f;
     if (bp) ldv<float, V>(bp, q);
 #pragma unroll
     for (int e = 0; e < V; ++e) q[e] += sum[e];
@@ -259,23 +286,26 @@ __global__ void pool_bwd_kernel(PoolBwdArgs a) {
   }
 }
 
+template <typename T>
+static void pool_bwd_go(const PoolBwdArgs &a, int V, unsigned g, hipStream_t s) {
+  if (V == 8) pool_bwd_kernel<T, 8><<<g, 256, 0, s>>>(a);
+  else if (V == 4) pool_bwd_kernel<T, 4><<<g, 256, 0, s>>>(a);
+  else pool_bwd_kernel<T, 1><<<g, 256, 0, s>>>(a);
+}
+
 int launch_pool_bwd(int dt, const PoolBwdArgs &a0, void *stream) {
   const long long total = (long long)a0.B * (a0.ub - a0.ua) * a0.Wu * a0.C;
   if (total <= 0) return 0;
   PoolBwdArgs a = a0;
-  a.fcv = fast_div((uint32_t)(a.C % 4 == 0 ? a.C / 4 : a.C));
+  // whole 16-byte storage vectors per thread when the channels fill them
+  const int V = dt == DT_BF16 && a.C % 8 == 0 ? 8 : a.C % 4 == 0 ? 4 : 1;
+  a.fcv = fast_div((uint32_t)(a.C / V));
   a.fw = fast_div((uint32_t)a.Wu);
   a.fr = fast_div((uint32_t)(a.ub - a.ua));
   hipStream_t s = (hipStream_t)stream;
-  const bool v4 = a.C % 4 == 0;
-  const unsigned g = grid_for(v4 ? total / 4 : total);
-  if (dt == DT_F32) {
-    if (v4) pool_bwd_kernel<float, 4><<<g, 256, 0, s>>>(a);
-    else pool_bwd_kernel<float, 1><<<g, 256, 0, s>>>(a);
-  } else {
-    if (v4) pool_bwd_kernel<bf16, 4><<<g, 256, 0, s>>>(a);
-    else pool_bwd_kernel<bf16, 1><<<g, 256, 0, s>>>(a);
-  }
+  const unsigned g = grid_for(total / V);
+  if (dt == DT_F32) pool_bwd_go<float>(a, V, g, s);
+  else pool_bwd_go<bf16>(a, V, g, s);
   return (int)hipGetLastError();
 }
 
@@ -320,43 +350,67 @@ int launch_add_fwd(int dt, View a, View b, View z, int relu, uint8_t *mask,
   return (int)hipGetLastError();
 }
 
-// One input side of the residual add's backward: either accumulate the
-// error into the input's float32 window (dc == nullptr), or, when the input
-// is a conv without ReLU whose only consumer is this add, write that conv's
-// error operand rnd(scale[c] * d) directly (contiguous own rows, the layout
-// act_bwd_kernel writes), which makes its window and its act_bwd pass
-// unnecessary.
-template <typename T, int V>
-__device__ __forceinline__ void add_bwd_side(const AddSide &sd, long long idx, int in, int b,
-                                             int y, const float (&d)[4]) {
-  if (sd.dc) {
-    float e[4];
+// Channel of the first of V consecutive elements of a row, and whether all
+// V lie in one pixel (C a multiple of V), so one division serves them all.
+template <int V, int N>
+__device__ __forceinline__ void scale_by(const float *scale, int in, int C, float (&d)[N]) {
+  if (C % V == 0) {
+    const int n = in % C;
 #pragma unroll
-    for (int k = 0; k < V; ++k) e[k] = sd.scale ? d[k] * sd.scale[(in + k) % sd.C] : d[k];
-    stv<T, V>((T *)sd.dc + idx * V, e);
+    for (int e = 0; e < V; ++e) d[e] *= scale[n + e];
   } else {
-    float x[4] = {0.f, 0.f, 0.f, 0.f};
-    float *p = (float *)sd.win.p + view_off(sd.win, b, y, in);
-    const float *bp = err_base(sd.init, sd.cinit, sd.cinit_t, b, y, in, p);
-    if (bp) ldv<float, V>(bp, x);
 #pragma unroll
-    for (int k = 0; k < V; ++k) x[k] += d[k];
-    stv<float, V>(p, x);
+    for (int e = 0; e < V; ++e) d[e] *= scale[(in + e) % C];
   }
 }
 
-// A window row above the add's rows: its initial value (carry or zero).
-template <int V>
-__device__ __forceinline__ void add_init_row(const AddSide &sd, const RowIter &e, long long j) {
-  int b, y, in;
-  e.at(j, V, b, y, in);
-  float x[4] = {0.f, 0.f, 0.f, 0.f};
+// The error d of one input side of a residual add at (b, y, in).
+template <typename T, int V, int N>
+__device__ __forceinline__ void add_bwd_side(const AddSide &sd, int in, int b, int y,
+                                             const float (&d)[N]) {
+  if (sd.skip) return;
+  float x[V];
+  if (sd.eo.fact) {
+#pragma unroll
+    for (int k = 0; k < V; ++k) x[k] = d[k];
+    if (y < sd.eo.fa) {
+      stv<float, V>((float *)sd.eo.carry.p + view_off(sd.eo.carry, b, y, in), x);
+    } else {
+      if (sd.eo.scale) scale_by<V>(sd.eo.scale, in, sd.eo.dc.C, x);
+      stv<T, V>((T *)sd.eo.dc.p + view_off(sd.eo.dc, b, y, in), x);
+    }
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < V; ++k) x[k] = 0.f;
   float *p = (float *)sd.win.p + view_off(sd.win, b, y, in);
-  const float *bp = err_base(1, sd.cinit, sd.cinit_t, b, y, in, p);
+  const float *bp = err_base(sd.init, sd.cinit, sd.cinit_t, b, y, in, p);
   if (bp) ldv<float, V>(bp, x);
+#pragma unroll
+  for (int k = 0; k < V; ++k) x[k] += d[k];
   stv<float, V>(p, x);
 }
 
+// A row past the add's own: what the band below carried in, or zero, goes
+// where the side's errors go.
+template <typename T, int V>
+__device__ __forceinline__ void add_init_row(const AddSide &sd, const RowIter &e, long long j) {
+  int b, y, in;
+  e.at(j, V, b, y, in);
+  float x[V];
+#pragma unroll
+  for (int k = 0; k < V; ++k) x[k] = 0.f;
+  const float *bp = err_base(1, sd.cinit, sd.cinit_t, b, y, in, nullptr);
+  if (bp) ldv<float, V>(bp, x);
+  if (sd.eo.fact) add_bwd_side<T, V>(sd, in, b, y, x);
+  else stv<float, V>((float *)sd.win.p + view_off(sd.win, b, y, in), x);
+}
+
+// HBM-bound: dz and z read once, one write per side (16 bytes per thread and
+// tensor in bfloat16). Completing a projection's error here, instead of
+// through its float32 window and an activation pass, together with dL/dy
+// read in place: ResNet-50's first block at 8 x 600 x 900, 32 bands, 22.9 ->
+// 16.9 ms per step.
 template <typename T, int V>
 __global__ void add_bwd_kernel(View dz, View z, AddSide sa, AddSide sb, int relu, RowIter it,
                                RowIter ea, RowIter eb) {
@@ -364,43 +418,55 @@ __global__ void add_bwd_kernel(View dz, View z, AddSide sa, AddSide sb, int relu
     int b, y, in;
     if (idx >= it.total) {
       const long long j = idx - it.total;
-      if (j < ea.total) add_init_row<V>(sa, ea, j);
-      else add_init_row<V>(sb, eb, j - ea.total);
+      if (j < ea.total) add_init_row<T, V>(sa, ea, j);
+      else add_init_row<T, V>(sb, eb, j - ea.total);
       continue;
     }
     it.at(idx, V, b, y, in);
-    float d[4], zz[4];
-    ldv<float, V>((const float *)dz.p + view_off(dz, b, y, in), d);
+    float d[V], zz[V];
+    ld_err<T, V>(dz, b, y, in, d);
     if (relu) {
       ldv<T, V>((const T *)z.p + view_off(z, b, y, in), zz);
 #pragma unroll
       for (int e = 0; e < V; ++e)
         if (!(zz[e] > 0.f)) d[e] = 0.f;
     }
-    add_bwd_side<T, V>(sa, idx, in, b, y, d);
-    add_bwd_side<T, V>(sb, idx, in, b, y, d);
+    add_bwd_side<T, V>(sa, in, b, y, d);
+    add_bwd_side<T, V>(sb, in, b, y, d);
   }
+}
+
+// Elements per thread of a row kernel: 16-byte storage vectors (8 bfloat16)
+// when the rows hold whole ones, else 4 or 1 elements.
+static int row_vec(int dt, int W, int C) {
+  const long long n = (long long)W * C;
+  return dt == DT_BF16 && n % 8 == 0 ? 8 : n % 4 == 0 ? 4 : 1;
+}
+
+template <typename T>
+static void add_bwd_go(int V, unsigned g, hipStream_t s, const View &dz, const View &z,
+                       const AddSide &sa, const AddSide &sb, int relu, const RowIter &it,
+                       const RowIter &ea, const RowIter &eb) {
+  if (V == 8) add_bwd_kernel<T, 8><<<g, 256, 0, s>>>(dz, z, sa, sb, relu, it, ea, eb);
+  else if (V == 4) add_bwd_kernel<T, 4><<<g, 256, 0, s>>>(dz, z, sa, sb, relu, it, ea, eb);
+  else add_bwd_kernel<T, 1><<<g, 256, 0, s>>>(dz, z, sa, sb, relu, it, ea, eb);
 }
 
 int launch_add_bwd(int dt, View dz, View z, const AddSide &sa, const AddSide &sb, int relu,
                    int B, int y0, int y1, int W, int C, void *stream) {
-  const int V = ((long long)W * C) % 4 == 0 ? 4 : 1;
+  const int V = row_vec(dt, W, C);
   RowIter it = row_iter(B, y0, y1, W, C, V);
-  if (it.total <= 0) return 0;
-  // initialised rows above the add's rows: window sides with init only
+  if (it.total <= 0 || (sa.skip && sb.skip)) return 0;
+  // rows past the add's own: initialised windows and complete errors only
   for (const AddSide *sd : {&sa, &sb})
-    if (sd->init_hi > y1 && (!sd->init || sd->dc)) return (int)hipErrorInvalidValue;
-  const RowIter ea = row_iter(B, y1, std::max(y1, sa.init_hi), W, C, V);
-  const RowIter eb = row_iter(B, y1, std::max(y1, sb.init_hi), W, C, V);
+    if (!sd->skip && sd->init_hi > y1 && !sd->init && !sd->eo.fact)
+      return (int)hipErrorInvalidValue;
+  const RowIter ea = row_iter(B, y1, sa.skip ? y1 : std::max(y1, sa.init_hi), W, C, V);
+  const RowIter eb = row_iter(B, y1, sb.skip ? y1 : std::max(y1, sb.init_hi), W, C, V);
   hipStream_t s = (hipStream_t)stream;
   const unsigned g = grid_for(it.total + ea.total + eb.total);
-  if (dt == DT_F32) {
-    if (V == 4) add_bwd_kernel<float, 4><<<g, 256, 0, s>>>(dz, z, sa, sb, relu, it, ea, eb);
-    else add_bwd_kernel<float, 1><<<g, 256, 0, s>>>(dz, z, sa, sb, relu, it, ea, eb);
-  } else {
-    if (V == 4) add_bwd_kernel<bf16, 4><<<g, 256, 0, s>>>(dz, z, sa, sb, relu, it, ea, eb);
-    else add_bwd_kernel<bf16, 1><<<g, 256, 0, s>>>(dz, z, sa, sb, relu, it, ea, eb);
-  }
+  if (dt == DT_F32) add_bwd_go<float>(V, g, s, dz, z, sa, sb, relu, it, ea, eb);
+  else add_bwd_go<bf16>(V, g, s, dz, z, sa, sb, relu, it, ea, eb);
   return (int)hipGetLastError();
 }
 
@@ -412,50 +478,48 @@ __global__ void act_bwd_kernel(View dz, View z, const float *scale, int relu, T 
                                int C, RowIter it, View cdst, RowIter cit) {
   GRID_STRIDE(idx, it.total + cit.total) {
     int b, y, in;
-    float d[4], zz[4];
+    float d[V], zz[V];
     if (idx >= it.total) {
       cit.at(idx - it.total, V, b, y, in);
-      ldv<float, V>((const float *)dz.p + view_off(dz, b, y, in), d);
+      ld_err<T, V>(dz, b, y, in, d);
       stv<float, V>((float *)cdst.p + view_off(cdst, b, y, in), d);
       continue;
     }
     it.at(idx, V, b, y, in);
-    ldv<float, V>((const float *)dz.p + view_off(dz, b, y, in), d);
+    ld_err<T, V>(dz, b, y, in, d);
     if (relu) {
       ldv<T, V>((const T *)z.p + view_off(z, b, y, in), zz);
 #pragma unroll
       for (int e = 0; e < V; ++e)
         if (!(zz[e] > 0.f)) d[e] = 0.f;
     }
-    if (scale) {
-#pragma unroll
-      for (int e = 0; e < V; ++e) d[e] *= scale[(in + e) % C];
-    }
+    if (scale) scale_by<V>(scale, in, C, d);
     stv<T, V>(dc + idx * V, d);
   }
+}
+
+template <typename T>
+static void act_bwd_go(int V, unsigned g, hipStream_t s, const View &dz, const View &z,
+                       const float *scale, int relu, void *dc, int C, const RowIter &it,
+                       const View &cd, const RowIter &cit) {
+  if (V == 8) act_bwd_kernel<T, 8><<<g, 256, 0, s>>>(dz, z, scale, relu, (T *)dc, C, it, cd, cit);
+  else if (V == 4)
+    act_bwd_kernel<T, 4><<<g, 256, 0, s>>>(dz, z, scale, relu, (T *)dc, C, it, cd, cit);
+  else act_bwd_kernel<T, 1><<<g, 256, 0, s>>>(dz, z, scale, relu, (T *)dc, C, it, cd, cit);
 }
 
 int launch_act_bwd(int dt, View dz, View z, const float *scale, int relu,
                    void *dc, int B, int y0, int y1, int W, int C, void *stream,
                    const View *carry, int c0, int c1) {
-  const int V = ((long long)W * C) % 4 == 0 ? 4 : 1;
+  const int V = row_vec(dt, W, C);
   RowIter it = row_iter(B, y0, y1, W, C, V);
   RowIter cit = row_iter(B, c0, carry ? c1 : c0, W, C, V);
   const View cd = carry ? *carry : View{};
   if (it.total + cit.total <= 0) return 0;
   hipStream_t s = (hipStream_t)stream;
   const unsigned g = grid_for(it.total + cit.total);
-  if (dt == DT_F32) {
-    if (V == 4)
-      act_bwd_kernel<float, 4><<<g, 256, 0, s>>>(dz, z, scale, relu, (float *)dc, C, it, cd, cit);
-    else
-      act_bwd_kernel<float, 1><<<g, 256, 0, s>>>(dz, z, scale, relu, (float *)dc, C, it, cd, cit);
-  } else {
-    if (V == 4)
-      act_bwd_kernel<bf16, 4><<<g, 256, 0, s>>>(dz, z, scale, relu, (bf16 *)dc, C, it, cd, cit);
-    else
-      act_bwd_kernel<bf16, 1><<<g, 256, 0, s>>>(dz, z, scale, relu, (bf16 *)dc, C, it, cd, cit);
-  }
+  if (dt == DT_F32) act_bwd_go<float>(V, g, s, dz, z, scale, relu, dc, C, it, cd, cit);
+  else act_bwd_go<bf16>(V, g, s, dz, z, scale, relu, dc, C, it, cd, cit);
   return (int)hipGetLastError();
 }
 

@@ -65,6 +65,10 @@ struct View {
   int row0;
   int W, C;
   int rows;  // rows held: [row0, row0 + rows); checked on the host only
+  // an error that a backward launch reads: 0 = float32 window, 1 = storage
+  // dtype (dL/dy of the last node, read in place instead of being copied
+  // into a window first)
+  int st = 0;
 };
 
 enum Dt { DT_F32 = 0, DT_BF16 = 1 };
@@ -387,25 +391,28 @@ int launch_pool_bwd(int dt, const PoolBwdArgs &a, void *stream);
 int launch_add_fwd(int dt, View a, View b, View z, int relu, uint8_t *mask,
                    int mask_h, int B, int y0, int y1, int W, int C,
                    void *stream);
-// d = dz * [z > 0] over rows [y0, y1), sent to both inputs of the add:
-// win += d (float32 window), or, when dc is set, dc = rnd(scale[c] * d)
-// written contiguously over the rows (the error operand of a conv input
-// without ReLU whose only consumer is the add; scale nullable, C channels).
+// d = dz * [z > 0] over rows [y0, y1), sent to both inputs of the add.
+// Three kinds of side:
+//   skip: nobody reads this input's error;
+//   eo.fact = 0: win += d (float32 window), or, with init = 1, win = the
+//     initial value (the float32 carry from rows >= cinit_t when cinit.p is
+//     set, else zero) plus d;
+//   eo.fact = 1: the input is a conv without ReLU whose only consumer is the
+//     add. Its error is complete here, so rows >= eo.fa go out as its error
+//     operand eo.dc = rnd(scale[c] * d) and rows < eo.fa as float32 to
+//     eo.carry (the band above owns them).
+// Rows [y1, init_hi) of a side (0 = none), which lie past the add's own rows
+// (a consumer with later rows, or a conv that owns them already, reaches
+// them), hold only what the band below carried in; they get it in the same
+// launch, from cinit (rows >= cinit_t) or as zero.
 struct AddSide {
   View win;
-  void *dc;
-  const float *scale;
-  int C;
-  // window path: init = 1 stores the initial value (the float32 carry from
-  // rows >= cinit_t when cinit.p is set, else zero) plus the error instead
-  // of adding to the window
+  int skip;
   int init;
   View cinit;
   int cinit_t;
-  // with init = 1: rows [y1, init_hi) of the window, above the add's rows,
-  // get their initial value alone in the same launch (the window's rows
-  // start at y0 and end at init_hi); 0 = none
   int init_hi;
+  ErrOut eo;
 };
 int launch_add_bwd(int dt, View dz, View z, const AddSide &sa, const AddSide &sb, int relu,
                    int B, int y0, int y1, int W, int C, void *stream);

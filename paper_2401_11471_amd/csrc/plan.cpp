@@ -459,11 +459,18 @@ static void layout(Plan &P, Layout &L, const Fuse &F, const std::vector<int> &ca
         const int rows_fit = (int)std::max<size_t>(1, lw_part / row_part);
         L.fchunk[v] = rows_fit < sv.h ? rows_fit : 0;
       }
-      std::vector<Rows> qs;
-      if (layerwise) qs.push_back(Rows{0, sv.h, 0, sv.h});
+      std::vector<Rows> qs, qus;
+      if (layerwise) {
+        qs.push_back(Rows{0, sv.h, 0, sv.h});
+        qus.push_back(Rows{0, su.h, 0, su.h});
+      }
       for (auto *tab : bands)
-        for (auto &br : *tab) qs.push_back(br[v]);
-      for (const Rows &q : qs) {
+        for (auto &br : *tab) {
+          qs.push_back(br[v]);
+          qus.push_back(br[d.in0]);
+        }
+      for (size_t i = 0; i < qs.size(); ++i) {
+        const Rows &q = qs[i], &qu = qus[i];
         if (q.b <= q.a) continue;
         const long long mf = (long long)P.cfg.batch * (q.b - q.a) * sv.w;
         const int sw_ = wgrad_split_count(d.c_out, nw, mf, pcap, P.es);
@@ -472,9 +479,15 @@ static void layout(Plan &P, Layout &L, const Fuse &F, const std::vector<int> &ca
         const int u0 = std::max(0, q.a * d.sh - d.ph);
         const int u1 = std::min(su.h, (q.b - 1) * d.sh - d.ph + d.kh);
         if (padded) xrows = std::max(xrows, u1 - u0);
-        const long long md = (long long)P.cfg.batch * (u1 - u0) * su.w;
-        const int sd = conv_split_count(md, su.c, conv_k_iters(taps, sv.c, P.es, true), pcap, P.es);
-        if (sd > 1) part = std::max(part, (size_t)(sd * md * su.c * 4));
+        // input gradient: over the rows the windows reach, or over the whole
+        // error window when the launch initializes it
+        for (const int rows_ : {u1 - u0, bwd_covers(u0, u1, qu.lo, qu.hi) ? qu.hi - qu.lo : 0}) {
+          const long long md = (long long)P.cfg.batch * rows_ * su.w;
+          if (md <= 0) continue;
+          const int sd =
+              conv_split_count(md, su.c, conv_k_iters(taps, sv.c, P.es, true), pcap, P.es);
+          if (sd > 1) part = std::max(part, (size_t)(sd * md * su.c * 4));
+        }
       }
     }
   if (layerwise) part = lw_part;
@@ -506,7 +519,7 @@ static void layout(Plan &P, Layout &L, const Fuse &F, const std::vector<int> &ca
   for (int v = 0; v < n; ++v)
     if (carry[v] > 0) {
       L.carry[v] = A.take(P.elems(v, carry[v]) * 4);
-      if (F.act[v] != 0) L.carry2[v] = A.take(P.elems(v, carry[v]) * 4);
+      if (F.act[v] != 0 || F.add[v] != 0) L.carry2[v] = A.take(P.elems(v, carry[v]) * 4);
     }
   L.carry_bytes = A.top - k0;
   // BP arena, packed by lifetime over the backward steps (step s handles
@@ -524,8 +537,11 @@ static void layout(Plan &P, Layout &L, const Fuse &F, const std::vector<int> &ca
     // (an act-fused conv's error window only stages the rows its consumer's
     // input gradient carries out, which the launch may not write into the
     // carry buffer it reads the rows carried in from)
+    // (the last node's error is dL/dy, and a conv whose error operand the
+    // add's backward writes has no window)
     const bool staged = F.act[v] != 0;
-    bufs[v] = LiveBuf{n - 1 - first, n - 1 - v, P.elems(v, staged ? carry[v] : cap[v]) * 4, 0};
+    const int rows_ = v == n - 1 || F.add[v] ? 0 : staged ? carry[v] : cap[v];
+    bufs[v] = LiveBuf{n - 1 - first, n - 1 - v, P.elems(v, rows_) * 4, 0};
   }
   std::vector<int> dc_i(n, -1), wp_i(n, -1);
   for (int v = 1; v < n; ++v) {
@@ -591,9 +607,11 @@ static void layout(Plan &P, Layout &L, const Fuse &F, const std::vector<int> &ca
 
 // Fusions of a schedule whose backward bands have rows `rows` and forward
 // bands `rows_fp` (act_ok: the schedule may form a conv's error operand in
-// its consumer's backward launch -- CARRY and layer-wise).
+// its consumer's backward launch -- CARRY and layer-wise; carry: errors are
+// carried between bands, P.tail).
 static Fuse decide_fusions(const Plan &P, const std::vector<std::vector<Rows>> &rows,
-                           const std::vector<std::vector<Rows>> &rows_fp, bool act_ok) {
+                           const std::vector<std::vector<Rows>> &rows_fp, bool act_ok,
+                           bool carry) {
   const int n = P.n, nb = (int)rows.size();
   Fuse F;
   // convs whose error operand the residual add's backward can write
@@ -603,14 +621,25 @@ static Fuse decide_fusions(const Plan &P, const std::vector<std::vector<Rows>> &
     if (d.op != LRCNN_OP_CONV || d.relu || P.cons[v].size() != 1) continue;
     const int c = P.cons[v][0];
     if (P.nodes[c].op != LRCNN_OP_ADD || P.nodes[c].in0 == P.nodes[c].in1) continue;
+    // v's window starts with the add's rows in every band: v owns the same
+    // rows, or owns rows later than the add reads them (the other input's
+    // branch is behind) and carries those errors to the band above. The
+    // add's launch must exist wherever v has rows.
     bool ok = true;
-    for (int r = 0; r < nb && ok; ++r) ok = rows[r][v].lo == rows[r][v].a;
+    for (int r = 0; r < nb && ok; ++r) {
+      const Rows &qv = rows[r][v], &qc = rows[r][c];
+      if (qc.b > qc.a)
+        ok = qv.lo == qc.a && qv.b >= qc.b && qv.hi == qv.b && (carry || qv.lo == qv.a) &&
+             (!carry || r + 1 == nb || P.tail[r][v] == qc.b);
+      else
+        ok = qv.b <= qv.a && qv.lo == qv.a;
+    }
     if (ok) F.add[v] = c;
   }
   F.fwd.assign(n, 0);
   for (int v = 1; v < n; ++v) {
     const int c = F.add[v];
-    if (!c || v != std::max(P.nodes[c].in0, P.nodes[c].in1)) continue;
+    if (!c) continue;
     if (P.shp[v].c % (16 / P.es) != 0) continue;
     bool ok = true;
     for (int r = 0; r < nb && ok; ++r)
@@ -618,7 +647,11 @@ static Fuse decide_fusions(const Plan &P, const std::vector<std::vector<Rows>> &
     for (size_t r = 0; r < rows_fp.size() && ok; ++r)
       ok = rows_fp[r][v].a == rows_fp[r][c].a && rows_fp[r][v].b == rows_fp[r][c].b &&
            rows_fp[r][v].lo == rows_fp[r][v].a;
-    if (ok) F.fwd[v] = c;
+    // (in node order, so the add's later input is the one kept)
+    if (ok) {
+      F.fwd[std::min(P.nodes[c].in0, P.nodes[c].in1)] = 0;
+      F.fwd[v] = c;
+    }
   }
   // convs whose error operand the backward launch of their only consumer v
   // (a conv's input gradient, a max-pool's backward) forms: in every band
@@ -639,7 +672,7 @@ static Fuse decide_fusions(const Plan &P, const std::vector<std::vector<Rows>> &
         if (qv.b > qv.a) {
           const int y0 = std::max(0, qv.a * d.sh - d.ph);
           const int y1 = std::min(hu, (qv.b - 1) * d.sh - d.ph + d.kh);
-          ok = y0 == qu.lo && y1 == qu.hi && qu.hi == qu.b && qu.lo <= qu.a;
+          ok = bwd_covers(y0, y1, qu.lo, qu.hi) && qu.hi == qu.b && qu.lo <= qu.a;
         } else {
           ok = qu.b <= qu.a && qu.lo == qu.a;
         }
@@ -809,12 +842,12 @@ static void finish(Plan &P, const std::vector<int> &bd, const std::vector<int> &
   P.rows_fp = P.rows;
   if (carry) carry_rows(P, bb); else cone_rows(P, bb);
   const int nb = P.nb;
-  P.fz = decide_fusions(P, P.rows, P.rows_fp, carry);
+  P.fz = decide_fusions(P, P.rows, P.rows_fp, carry, carry);
   {
     // the layer-wise schedule: one band of whole maps
     std::vector<std::vector<Rows>> whole(1, std::vector<Rows>(n));
     for (int v = 0; v < n; ++v) whole[0][v] = Rows{0, P.shp[v].h, 0, P.shp[v].h};
-    P.fz_lw = decide_fusions(P, whole, whole, true);
+    P.fz_lw = decide_fusions(P, whole, whole, true, false);
   }
   // capacities
   std::vector<int> cap(n, 0), own(n, 0), cry(n, 0), fcap(n, 0);

@@ -65,12 +65,13 @@ struct Layout {
 
 // Fusions of a schedule (decided from that schedule's own rows, so the
 // layer-wise baseline does not depend on the row partition):
-//  add[u]: the ADD node whose backward writes conv u's error operand
-//          directly (a conv without ReLU whose only consumer is that add
-//          and that carries no rows between backward bands), else 0
-//  fwd[u]: the ADD node whose forward conv u's epilogue computes (the add's
-//          later input, fused in its backward, same rows in every band and
-//          whole 16-byte channel vectors), else 0
+//  add[u]: the ADD node whose backward writes conv u's error operand (and
+//          the rows u carries between backward bands) directly (a conv
+//          without ReLU whose only consumer is that add), else 0
+//  fwd[u]: the ADD node whose forward conv u's epilogue computes (one of the
+//          add's inputs, fused in its backward, same rows in every band and
+//          whole 16-byte channel vectors; the later input when both
+//          qualify, and an earlier one runs at the add's step), else 0
 //  act[u]: (CARRY / layer-wise) conv u's only consumer, a conv or max-pool
 //          v, whose backward launch forms u's error operand and carry
 //          directly (when that launch initializes u's whole error window);
@@ -137,6 +138,17 @@ struct Plan {
     return (size_t)cfg.batch * rows_ * shp[v].w * shp[v].c;
   }
 };
+
+// Whether a backward launch whose windows reach producer rows [y0, y1) runs
+// over the whole error window [lo, hi) instead, so that it initializes it:
+// rows outside [y0, y1) get only the carried error (a window row that this
+// band's consumer rows do not reach, e.g. the odd row before a stride-2
+// window). The extra rows cost a conv's input gradient their share of the
+// launch, an initialization pass costs a read and a write of the window and
+// a launch, so at most a quarter more rows (one at least) are taken.
+inline bool bwd_covers(int y0, int y1, int lo, int hi) {
+  return y0 >= lo && y1 <= hi && (hi - lo) - (y1 - y0) <= ((y1 - y0) / 4 > 1 ? (y1 - y0) / 4 : 1);
+}
 
 // Releases the executor's side stream and events of a plan (exec.cpp).
 void release_side(Plan &P);
