@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdint>
 #include <string>
+#include <type_traits>
 
 #include "lrcnn.h"
 #include "plan.hpp"
@@ -19,7 +20,17 @@ namespace lrcnn {
 namespace {
 
 constexpr int kMaxClasses = 64;
-constexpr int kChunk = 8192;  // features per block of the logits pass
+// Features per block of the logits pass. The pass reads every class's
+// weights once per image (from L2 after the first) and is bound by how many
+// blocks share that: VGG-16's 25088 features and 8 images make 104 blocks
+// of 2048 (32 blocks of kWsChunk left the chip idle: 143 us, and the float32
+// training step on VGG-16's last block 1.43 ms; now 1.22 ms with the fused
+// passes below). The partial sums of
+// the finer chunks go into dy, which the last pass of the call overwrites:
+// K / 2048 x 64 classes x 4 bytes per image always fit its K x 2 bytes. With
+// K <= 2048 there is one chunk, and it goes to the workspace, which holds
+// the sums of chunks of kWsChunk features.
+constexpr int kChunk = 2048, kWsChunk = 8192;
 
 typedef uint16_t bf16;
 __device__ __forceinline__ float ld(const float *p) { return *p; }
@@ -38,14 +49,51 @@ __device__ __forceinline__ void st(bf16 *p, float f) {
   *p = (bf16)(u >> 16);
 }
 
+// N consecutive values (4: one access)
+template <int N>
+__device__ __forceinline__ void ldn(const float *p, float (&v)[N]) {
+  if constexpr (N == 4) {
+    const float4 q = *(const float4 *)p;
+    v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
+  } else {
+    v[0] = *p;
+  }
+}
+template <int N>
+__device__ __forceinline__ void ldn(const bf16 *p, float (&v)[N]) {
+  if constexpr (N == 4) {
+    const uint2 q = *(const uint2 *)p;
+    v[0] = __uint_as_float(q.x << 16), v[1] = __uint_as_float(q.x & 0xffff0000u);
+    v[2] = __uint_as_float(q.y << 16), v[3] = __uint_as_float(q.y & 0xffff0000u);
+  } else {
+    v[0] = ld(p);
+  }
+}
+template <int N>
+__device__ __forceinline__ void stn(float *p, const float (&v)[N]) {
+  if constexpr (N == 4) *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]);
+  else *p = v[0];
+}
+template <int N>
+__device__ __forceinline__ void stn(bf16 *p, const float (&v)[N]) {
+  bf16 t[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) st(t + i, v[i]);
+  if constexpr (N == 4)
+    *(uint2 *)p = make_uint2((uint32_t)t[0] | ((uint32_t)t[1] << 16),
+                             (uint32_t)t[2] | ((uint32_t)t[3] << 16));
+  else *p = t[0];
+}
+
 // part[b][chunk][c] = sum over the chunk's features k of y[b, k] * fc_w[c, k]:
-// each thread sums its strided features, the block's 256 sums of a class
-// are then added in thread order.
-template <typename T>
+// each thread sums its strided vectors of V features, a wave its lanes' sums
+// as a fixed tree, and the four waves' sums are added in order. (Thread
+// after thread in LDS, the 256 sums of a class took 7 us by themselves.)
+template <typename T, int V>
 __global__ __launch_bounds__(256) void head_partial_kernel(const T *y, const float *fw,
                                                            long long K, int C, int chunks,
                                                            float *part) {
-  __shared__ float red[kMaxClasses][257];
+  __shared__ float red[kMaxClasses][4];
   const int ch = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const long long k0 = (long long)ch * kChunk;
   const long long k1 = k0 + kChunk < K ? k0 + kChunk : K;
@@ -53,27 +101,36 @@ __global__ __launch_bounds__(256) void head_partial_kernel(const T *y, const flo
 #pragma unroll
   for (int c = 0; c < kMaxClasses; ++c) acc[c] = 0.f;
   const T *yb = y + (long long)b * K;
-  for (long long k = k0 + tid; k < k1; k += 256) {
-    const float v = ld(yb + k);
+  for (long long k = k0 + tid * V; k < k1; k += 256 * V) {
+    float v[V];
+    ldn<V>(yb + k, v);
 #pragma unroll
     for (int c = 0; c < kMaxClasses; ++c)
-      if (c < C) acc[c] += v * fw[(long long)c * K + k];
+      if (c < C) {
+        float w[V];
+        ldn<V>(fw + (long long)c * K + k, w);
+#pragma unroll
+        for (int e = 0; e < V; ++e) acc[c] += v[e] * w[e];
+      }
   }
 #pragma unroll
   for (int c = 0; c < kMaxClasses; ++c)
-    if (c < C) red[c][tid] = acc[c];
+    if (c < C) {
+      float s = acc[c];
+#pragma unroll
+      for (int d = 32; d > 0; d >>= 1) s += __shfl_down(s, d);
+      if ((tid & 63) == 0) red[c][tid >> 6] = s;
+    }
   __syncthreads();
-  if (tid < C) {
-    float s = 0.f;
-    for (int t = 0; t < 256; ++t) s += red[tid][t];
-    part[((long long)b * chunks + ch) * C + tid] = s;
-  }
+  if (tid < C)
+    part[((long long)b * chunks + ch) * C + tid] =
+        ((red[tid][0] + red[tid][1]) + red[tid][2]) + red[tid][3];
 }
 
-// One block: logits, softmax, per-sample loss and dL/dlogits = (p - onehot)/B
-// for every sample, then the mean loss and dL/dfc_b (sums over samples in
-// sample order). A label outside [0, C) makes its loss term NaN; nothing is
-// read out of bounds.
+// One block: logits (a thread per image and class), softmax, per-sample loss
+// and dL/dlogits = (p - onehot)/B for every sample, then the mean loss and
+// dL/dfc_b (sums over samples in sample order). A label outside [0, C)
+// makes its loss term NaN; nothing is read out of bounds.
 __global__ __launch_bounds__(256) void head_softmax_kernel(const float *part, int chunks,
                                                            const float *fb,
                                                            const int32_t *labels, int B,
@@ -81,33 +138,29 @@ __global__ __launch_bounds__(256) void head_softmax_kernel(const float *part, in
                                                            float *lossv, float *loss,
                                                            float *dfb) {
   const int tid = threadIdx.x;
+  for (long long i = tid; i < (long long)B * C; i += 256) {
+    const long long b = i / C;
+    const int c = (int)(i - b * C);
+    float s = fb[c];
+#pragma unroll 8
+    for (int ch = 0; ch < chunks; ++ch) s += part[(b * chunks + ch) * C + c];
+    logits[i] = s;
+  }
+  __syncthreads();
   for (int b = tid; b < B; b += 256) {
-    float z[kMaxClasses];
+    const float *z = logits + (long long)b * C;
     float m = -INFINITY;
-#pragma unroll
-    for (int c = 0; c < kMaxClasses; ++c) {
-      if (c >= C) continue;
-      float s = fb[c];
-      for (int ch = 0; ch < chunks; ++ch) s += part[((long long)b * chunks + ch) * C + c];
-      z[c] = s;
-      logits[(long long)b * C + c] = s;
-      m = fmaxf(m, s);
-    }
+#pragma unroll 8
+    for (int c = 0; c < C; ++c) m = fmaxf(m, z[c]);
     float se = 0.f;
-#pragma unroll
-    for (int c = 0; c < kMaxClasses; ++c)
-      if (c < C) se += expf(z[c] - m);
+#pragma unroll 8
+    for (int c = 0; c < C; ++c) se += expf(z[c] - m);
     const int lab = labels[b];
     const float lse = m + logf(se);
-    float zl = NAN;
-#pragma unroll
-    for (int c = 0; c < kMaxClasses; ++c)
-      if (c < C && c == lab) zl = z[c];
-    lossv[b] = lse - zl;
-#pragma unroll
-    for (int c = 0; c < kMaxClasses; ++c)
-      if (c < C)
-        dlog[(long long)b * C + c] = (expf(z[c] - lse) - (c == lab ? 1.f : 0.f)) / (float)B;
+    lossv[b] = lse - (lab >= 0 && lab < C ? z[lab] : NAN);
+#pragma unroll 8
+    for (int c = 0; c < C; ++c)
+      dlog[(long long)b * C + c] = (expf(z[c] - lse) - (c == lab ? 1.f : 0.f)) / (float)B;
   }
   __syncthreads();
   if (tid == 0) {
@@ -122,41 +175,114 @@ __global__ __launch_bounds__(256) void head_softmax_kernel(const float *part, in
   }
 }
 
-// dy[b, k] = sum_c dlog[b, c] * fc_w[c, k] (storage dtype)
-template <typename T>
-__global__ void head_dy_kernel(const float *dlog, const float *fw, long long K, int B, int C,
-                               T *dy) {
-  const long long total = (long long)B * K;
+// dy[b, k] = sum_c dlog[b, c] * fc_w[c, k] (storage dtype) and
+// dfc_w[c, k] = sum_b dlog[b, c] * y[b, k], V features per thread, in one
+// launch (they do not depend on each other).
+template <typename T, int V>
+__global__ void head_grad_kernel(const float *dlog, const float *fw, const T *y, long long K,
+                                 int B, int C, T *dy, float *dfw) {
+  const long long KV = K / V, ny = (long long)B * KV, total = ny + (long long)C * KV;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
        i += (long long)gridDim.x * blockDim.x) {
-    const long long b = i / K, k = i - b * K;
-    float s = 0.f;
-    for (int c = 0; c < C; ++c) s += dlog[b * C + c] * fw[(long long)c * K + k];
-    st(dy + i, s);
+    const bool isy = i < ny;
+    const long long j = isy ? i : i - ny;
+    const long long r = j / KV, k = (j - r * KV) * V;
+    float s[V], v[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) s[e] = 0.f;
+    if (isy) {
+#pragma unroll 8
+      for (int c = 0; c < C; ++c) {
+        ldn<V>(fw + (long long)c * K + k, v);
+#pragma unroll
+        for (int e = 0; e < V; ++e) s[e] += dlog[r * C + c] * v[e];
+      }
+      stn<V>(dy + r * K + k, s);
+    } else {
+#pragma unroll 8
+      for (int b = 0; b < B; ++b) {
+        ldn<V>(y + (long long)b * K + k, v);
+#pragma unroll
+        for (int e = 0; e < V; ++e) s[e] += dlog[(long long)b * C + r] * v[e];
+      }
+      stn<V>(dfw + r * K + k, s);
+    }
   }
 }
 
-// dfc_w[c, k] = sum_b dlog[b, c] * y[b, k]
+// theta <- theta - lr * g for up to kSgdSegs parameter tensors in one launch
+// (a launch per tensor costs more than the tensor for all but the largest),
+// computed in float32 and stored in theta's dtype. Block runs of 1024
+// elements; a segment whose pointers are not 16-byte aligned goes element by
+// element.
+constexpr int kSgdSegs = 24;
+struct SgdSeg {
+  void *w;
+  const float *g;
+  long long n;
+  int bf, vec;
+};
+struct SgdBatch {
+  int n;
+  SgdSeg seg[kSgdSegs];
+  long long start[kSgdSegs + 1];  // first block run of each segment
+};
 template <typename T>
-__global__ void head_dw_kernel(const float *dlog, const T *y, long long K, int B, int C,
-                               float *dfw) {
-  const long long total = (long long)C * K;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    const long long c = i / K, k = i - c * K;
-    float s = 0.f;
-    for (int b = 0; b < B; ++b) s += dlog[(long long)b * C + c] * ld(y + (long long)b * K + k);
-    dfw[i] = s;
+__device__ __forceinline__ void sgd_run(const SgdSeg &g, long long i0, float lr) {
+  T *w = (T *)g.w;
+  const long long i = i0 + 4 * threadIdx.x;
+  if (g.vec && i + 4 <= g.n) {
+    float a[4], d[4];
+    ldn<4>(w + i, a);
+    ldn<4>(g.g + i, d);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] = a[e] - lr * d[e];
+    stn<4>(w + i, a);
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (i + e < g.n) st(w + i + e, ld(w + i + e) - lr * g.g[i + e]);
+}
+__global__ __launch_bounds__(256) void sgd_kernel(SgdBatch sb, float lr) {
+  for (long long r = blockIdx.x; r < sb.start[sb.n]; r += gridDim.x) {
+    int s = 0;
+    while (s + 1 < sb.n && r >= sb.start[s + 1]) ++s;
+    const SgdSeg &g = sb.seg[s];
+    const long long i0 = (r - sb.start[s]) * 1024;
+    if (g.bf) sgd_run<bf16>(g, i0, lr);
+    else sgd_run<float>(g, i0, lr);
   }
 }
 
-// theta <- theta - lr * g, computed in float32 and stored in theta's dtype
-template <typename T>
-__global__ void sgd_kernel(T *w, const float *g, long long n, float lr) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    st(w + i, ld(w + i) - lr * g[i]);
-}
+// Collects the tensors of one update; a tensor that overlaps one already
+// collected (shared weights) starts a new launch, so updates stay in order.
+struct SgdQueue {
+  SgdBatch b{};
+  float lr;
+  hipStream_t s;
+  void flush() {
+    if (b.n && b.start[b.n] > 0)
+      sgd_kernel<<<(unsigned)(b.start[b.n] < 65536 ? b.start[b.n] : 65536), 256, 0, s>>>(b, lr);
+    b.n = 0;
+  }
+  void add(void *w, const float *g, long long n, bool bf) {
+    if (n <= 0) return;
+    const uintptr_t lo = (uintptr_t)w, hi = lo + (uintptr_t)n * (bf ? 2 : 4);
+    bool over = b.n == kSgdSegs;
+    for (int i = 0; i < b.n && !over; ++i) {
+      const SgdSeg &q = b.seg[i];
+      const uintptr_t ql = (uintptr_t)q.w, qh = ql + (uintptr_t)q.n * (q.bf ? 2 : 4);
+      over = lo < qh && ql < hi;
+    }
+    if (over) flush();
+    if (b.n == 0) b.start[0] = 0;
+    const bool vec = ((uintptr_t)w & (bf ? 7 : 15)) == 0 && ((uintptr_t)g & 15) == 0;
+    b.seg[b.n] = SgdSeg{w, g, n, bf ? 1 : 0, vec ? 1 : 0};
+    b.start[b.n + 1] = b.start[b.n] + (n + 1023) / 1024;
+    ++b.n;
+  }
+};
 
 unsigned blocks_for(long long n) {
   long long g = (n + 255) / 256;
@@ -175,9 +301,10 @@ HeadLayout head_layout(const Plan &P, int C) {
   h.K = (long long)s.h * s.w * s.c;
   h.B = P.cfg.batch;
   h.chunks = (int)((h.K + kChunk - 1) / kChunk);
+  const int ws_chunks = (int)((h.K + kWsChunk - 1) / kWsChunk);
   auto a256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
   h.part = 0;
-  h.dlog = a256((size_t)h.B * h.chunks * C * 4);
+  h.dlog = a256((size_t)h.B * ws_chunks * C * 4);
   h.lossv = a256(h.dlog + (size_t)h.B * C * 4);
   h.total = a256(h.lossv + (size_t)h.B * 4);
   return h;
@@ -218,26 +345,32 @@ extern "C" int lrcnn_head_loss(const lrcnn_plan_t *plan, const void *y, const fl
                                             " bytes, got " + std::to_string(head_ws_bytes));
   hipStream_t s = (hipStream_t)stream;
   char *ws = (char *)head_ws;
-  float *part = (float *)(ws + h.part), *dlog = (float *)(ws + h.dlog),
+  float *part = h.chunks > 1 ? (float *)dy : (float *)(ws + h.part), *dlog = (float *)(ws + h.dlog),
         *lossv = (float *)(ws + h.lossv);
   const int C = n_classes;
   const bool bf = P.cfg.dtype == LRCNN_BF16;
   dim3 g1(h.chunks, h.B);
-  if (bf)
-    head_partial_kernel<bf16><<<g1, 256, 0, s>>>((const bf16 *)y, fc_w, h.K, C, h.chunks, part);
-  else
-    head_partial_kernel<float><<<g1, 256, 0, s>>>((const float *)y, fc_w, h.K, C, h.chunks,
-                                                  part);
+  // (4-wide accesses when every image's and class's row keeps them aligned)
+  const bool v4 = h.K % 4 == 0;
+  auto partial = [&](auto *yp) {
+    using T = std::remove_const_t<std::remove_pointer_t<decltype(yp)>>;
+    if (v4) head_partial_kernel<T, 4><<<g1, 256, 0, s>>>(yp, fc_w, h.K, C, h.chunks, part);
+    else head_partial_kernel<T, 1><<<g1, 256, 0, s>>>(yp, fc_w, h.K, C, h.chunks, part);
+  };
+  auto grads = [&](auto *yp) {
+    using T = std::remove_const_t<std::remove_pointer_t<decltype(yp)>>;
+    const unsigned g = blocks_for((long long)(h.B + C) * h.K / (v4 ? 4 : 1));
+    if (v4)
+      head_grad_kernel<T, 4><<<g, 256, 0, s>>>(dlog, fc_w, yp, h.K, h.B, C, (T *)dy, d_fc_w);
+    else
+      head_grad_kernel<T, 1><<<g, 256, 0, s>>>(dlog, fc_w, yp, h.K, h.B, C, (T *)dy, d_fc_w);
+  };
+  if (bf) partial((const bf16 *)y);
+  else partial((const float *)y);
   head_softmax_kernel<<<1, 256, 0, s>>>(part, h.chunks, fc_b, labels, h.B, C, logits, dlog,
                                         lossv, loss, d_fc_b);
-  const unsigned gd = blocks_for((long long)h.B * h.K), gw = blocks_for((long long)C * h.K);
-  if (bf) {
-    head_dy_kernel<bf16><<<gd, 256, 0, s>>>(dlog, fc_w, h.K, h.B, C, (bf16 *)dy);
-    head_dw_kernel<bf16><<<gw, 256, 0, s>>>(dlog, (const bf16 *)y, h.K, h.B, C, d_fc_w);
-  } else {
-    head_dy_kernel<float><<<gd, 256, 0, s>>>(dlog, fc_w, h.K, h.B, C, (float *)dy);
-    head_dw_kernel<float><<<gw, 256, 0, s>>>(dlog, (const float *)y, h.K, h.B, C, d_fc_w);
-  }
+  if (bf) grads((const bf16 *)y);
+  else grads((const float *)y);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess)
     return lrcnn_fail(LRCNN_EHIP, std::string("head: ") + hipGetErrorString(e));
@@ -253,24 +386,26 @@ extern "C" int lrcnn_sgd_update(const lrcnn_plan_t *plan, float lr, void *const 
   const Plan &P = *reinterpret_cast<const Plan *>(plan);
   hipStream_t s = (hipStream_t)stream;
   const bool bf = P.cfg.dtype == LRCNN_BF16;
+  SgdQueue q;
+  q.lr = lr;
+  q.s = s;
   for (int v = 1; v < P.n; ++v) {
     const lrcnn_node &d = P.nodes[v];
     if (d.op != LRCNN_OP_CONV) continue;
     if (!w[v] || !dw[v] || misaligned(w[v]) || misaligned(dw[v]))
       return lrcnn_fail(LRCNN_EINVAL, "weights or dw of node " + std::to_string(v) +
                                           " null or misaligned");
-    const long long n = (long long)d.c_out * d.kh * d.kw * P.shp[d.in0].c;
-    if (bf) sgd_kernel<bf16><<<blocks_for(n), 256, 0, s>>>((bf16 *)w[v], dw[v], n, lr);
-    else sgd_kernel<float><<<blocks_for(n), 256, 0, s>>>((float *)w[v], dw[v], n, lr);
+    q.add(w[v], dw[v], (long long)d.c_out * d.kh * d.kw * P.shp[d.in0].c, bf);
   }
   if (fc_w || fc_b) {
     if (!fc_w || !d_fc_w || !fc_b || !d_fc_b || n_classes < 1)
       return lrcnn_fail(LRCNN_EINVAL, "head parameters and gradients must all be given");
     const Shape &o = P.shp[P.n - 1];
     const long long nw = (long long)n_classes * o.h * o.w * o.c;
-    sgd_kernel<float><<<blocks_for(nw), 256, 0, s>>>(fc_w, d_fc_w, nw, lr);
-    sgd_kernel<float><<<1, 256, 0, s>>>(fc_b, d_fc_b, n_classes, lr);
+    q.add(fc_w, d_fc_w, nw, false);
+    q.add(fc_b, d_fc_b, n_classes, false);
   }
+  q.flush();
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess)
     return lrcnn_fail(LRCNN_EHIP, std::string("sgd: ") + hipGetErrorString(e));
