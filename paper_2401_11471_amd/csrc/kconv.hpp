@@ -249,13 +249,15 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
         const int sy = by[i] + (int)ti_, sx = bx[i] + (int)tj_;
         const bool ok = tok & am[i] & (sx >= 0) & (sy >= a.sy0) & (sy < a.sy1) & (sx < a.Ws);
         const long long off = rbase[i] + (long long)ti_ * srow + (long long)tj_ * a.src.C;
-        ra[i] = load16<T, false>(ok ? src + off : src, ok, a.KC);
+        if (sizeof(T) == 4 && a.KC == 3) ra[i] = load12(src + off, ok);
+        else ra[i] = load16<T, false>(ok ? src + off : src, ok, a.KC);
       }
 #pragma unroll
       for (int j = 0; j < NBL; ++j) {
         const bool ok = bvld[j] & tok;
         const long long off = bbase[j] - kv * E + (long long)tp * a.KC;
-        rb[j] = load16<T, false>(ok ? w + off : w, ok, a.KC);
+        if (sizeof(T) == 4 && a.KC == 3) rb[j] = load12(w + off, ok);
+        else rb[j] = load16<T, false>(ok ? w + off : w, ok, a.KC);
       }
       ++kpk;
       return;
@@ -832,6 +834,272 @@ static double conv_bytes(const ConvArgs &a, long long M, int splits, bool epi) {
   return in + w + (splits > 1 ? splits * mn * 4.0 : out);
 }
 
+// ------------------------------------------- first layer, bfloat16 forward
+// A convolution whose input channels fill no 16-byte vector (a 3-channel
+// image), K packed by kernel rows (conv_row_packed): vector v of kernel row
+// ti holds elements [8 v, 8 v + 8) of the row's kw * KC, which are contiguous
+// in the NHWC source row as in the weights. The weight tile (64 outputs x
+// all of K) is laid into LDS once per workgroup, which then walks pixel
+// tiles; the pixel operand needs no LDS at all: an MFMA lane wants 8
+// consecutive K elements of one pixel, i.e. one such vector, and fetches
+// them itself, so the K loop has no barrier. A vector starts at any 2-byte
+// address: it is fetched as the five aligned dwords around it and shifted
+// into place. Elements past the row's last belong to the next pixel and are
+// masked off (they may be NaN). Where a 32-pixel block of a wave has a
+// window that leaves the image, or whose dwords could leave the tensor, its
+// vectors are gathered element by element.
+// Wave tile: 32 MI pixels x 64 outputs. Bound by HBM (the output map) and
+// the shifting's VALU. One tap per vector with the operand staged through
+// LDS took 119 us for 38 rows of the ResNet-50 stem at 8 x 2400 x 3600; the
+// stem's training step there went 14.9 -> 10.4 ms, a 224-pixel forward of
+// ResNet-50 at batch 16 2.77 -> 2.71 ms, the static forward of stem and first
+// block on one 224-pixel image 111 -> 93 us.
+struct RawVec {
+  uint32_t d[5];
+  int sh;
+};
+__device__ __forceinline__ RawVec first_dwords(const bf16 *p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  typedef __attribute__((address_space(1))) const u32x4 g_u32x4;
+  typedef __attribute__((address_space(1))) const uint32_t g_u32;
+  const uintptr_t at = (uintptr_t)p & ~(uintptr_t)3;
+  const u32x4 q = *(g_u32x4 *)at;
+  RawVec r;
+  r.d[0] = q.x, r.d[1] = q.y, r.d[2] = q.z, r.d[3] = q.w;
+  r.d[4] = *(g_u32 *)(at + 16);
+  r.sh = ((uintptr_t)p & 2) ? 16 : 0;
+  return r;
+}
+// elements [lo, hi) of the vector at p, zeros elsewhere, already in place
+__device__ __forceinline__ RawVec first_elems(const bf16 *p, int lo, int hi) {
+  typedef __attribute__((address_space(1))) const bf16 g_bf16;
+  uint32_t e[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    e[k] = *(g_bf16 *)((k >= lo) & (k < hi) ? p + k : (const bf16 *)&g_zero16[0]);
+  RawVec r;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) r.d[k] = e[2 * k] | (e[2 * k + 1] << 16);
+  r.d[4] = 0;
+  r.sh = 0;
+  return r;
+}
+template <int MI>
+__global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tiles, int KP) {
+  // KP: K padded to whole 16-element slices; weight rows have a pitch of an
+  // odd number of 16-byte vectors (16 rows of a read on distinct banks)
+  extern __shared__ __align__(16) char smem[];
+  constexpr int SP = 64 + 8;  // staging pitch of a wave's 32 x 64 output block
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 31, g = lane >> 5;
+  const int RV = (int)a.fkw.d, rlen = a.kw * a.KC, nvec = a.kh * RV, KV = KP / 8;
+  const int WP = KP + 8;
+  bf16 *Ws = (bf16 *)smem;
+  bf16 *St = (bf16 *)(smem + 64 * WP * 2) + wave * 32 * SP;
+  const bf16 *src = (const bf16 *)a.src.p, *w = (const bf16 *)a.w;
+  const long long srow = (long long)a.src.W * a.src.C;
+  const int M = a.B * (a.y1 - a.y0) * a.Wd;
+  const int n0 = blockIdx.y * 64;
+  for (int i = tid; i < 64 * KV; i += 256) {
+    const int n = i / KV, q = i - n * KV;
+    uint32_t ti, v;
+    fdiv_qr((uint32_t)q, a.fkw, ti, v);
+    const bool ok = (n0 + n < a.N) & (q < nvec);
+    const bf16 *p = w + (long long)(n0 + n) * a.kh * rlen + (long long)ti * rlen + 8 * v;
+    const RawVec e = first_elems(p, 0, ok ? rlen - 8 * (int)v : 0);
+    *(uint4 *)(Ws + n * WP + 8 * q) = make_uint4(e.d[0], e.d[1], e.d[2], e.d[3]);
+  }
+  __syncthreads();
+  // elements of a kernel row's last vector, as masks of its dwords
+  const int nl = rlen - 8 * (RV - 1);
+  uint32_t lm[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) lm[k] = 2 * k + 1 < nl ? ~0u : 2 * k < nl ? 0xffffu : 0u;
+  // pixels past a window that the last vector's dwords reach
+  const int over = (RV * 8 + 2 - rlen + a.KC - 1) / a.KC;
+  float csc[2], csh[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int n = n0 + 32 * j + r;
+    const bool ok = a.scale && n < a.N;
+    csc[j] = ok ? a.scale[n] : 1.f;
+    csh[j] = ok ? a.shift[n] : 0.f;
+  }
+  const bool mask_vec = ((uintptr_t)a.mask & 7) == 0;
+  const long long drow = (long long)a.dst.W * a.N;
+  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int m0 = (t * 4 + wave) * 32 * MI;
+    const bf16 *rp[MI];  // element of tap (0, 0)
+    int by[MI], bx[MI];
+    bool am[MI], in[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int m = m0 + 32 * i + r;
+      am[i] = m < M;
+      uint32_t q, x, b, y;
+      fdiv_qr((uint32_t)(am[i] ? m : 0), a.fw, q, x);
+      fdiv_qr(q, a.fr, b, y);
+      by[i] = (a.y0 + (int)y) * a.sh - a.ph;
+      bx[i] = (int)x * a.sw - a.pw;
+      rp[i] = src + (long long)b * a.src.bs + (long long)(by[i] - a.src.row0) * srow +
+              (long long)bx[i] * a.src.C;
+      in[i] = __all(am[i] & (by[i] >= a.sy0) & (by[i] + a.kh <= a.sy1) & (bx[i] >= 0) &
+                    (bx[i] + a.kw + over <= a.Ws));
+    }
+    f32x16 acc[MI][2];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    // this lane's vector of a slice: kernel row ti, vector v of it
+    int ti = 0, v = g;
+    while (v >= RV) v -= RV, ++ti;
+    auto fetch = [&](RawVec (&raw)[MI]) {
+      const bool vok = ti < a.kh;
+      const int tr = vok ? ti : 0, e0 = 8 * v;
+      const long long ro = (long long)tr * srow + e0;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        if (in[i]) {
+          raw[i] = first_dwords(rp[i] + ro);
+        } else {
+          const int sy = by[i] + tr;
+          const bool ok = vok & am[i] & (sy >= a.sy0) & (sy < a.sy1);
+          const int lo = max(0, -bx[i]) * a.KC - e0;
+          const int hi = min(rlen, (a.Ws - bx[i]) * a.KC) - e0;
+          raw[i] = first_elems(rp[i] + ro, lo, ok ? hi : 0);
+        }
+      }
+    };
+    // (the masks of the fetched slice, then the next slice's vector)
+    auto masks = [&](uint32_t (&mk)[4]) {
+      const bool last = v == RV - 1, none = ti >= a.kh;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) mk[k] = none ? 0u : last ? lm[k] : ~0u;
+      v += 2;
+      while (v >= RV) v -= RV, ++ti;
+    };
+    RawVec cur[MI], nxt[MI];
+    uint32_t mc[4], mn[4];
+    fetch(cur);
+    masks(mc);
+    const int S = KP / 16;
+    for (int s = 0; s < S; ++s) {
+      if (s + 1 < S) {
+        fetch(nxt);
+        masks(mn);
+      }
+      bf16x8 bq[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        bq[j] = *(const bf16x8 *)(Ws + (32 * j + r) * WP + 16 * s + 8 * g);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        union {
+          uint32_t u[4];
+          bf16x8 v;
+        } q;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          q.u[k] = __builtin_amdgcn_alignbit(cur[i].d[k + 1], cur[i].d[k], cur[i].sh) & mc[k];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q.v, bq[j], acc[i][j], 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < MI; ++i) cur[i] = nxt[i];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) mc[k] = mn[k];
+    }
+    // epilogue, a wave's 32 x 64 block at a time through its own LDS slice
+    // (one wave's LDS accesses run in order; the fences keep the compiler
+    // from reordering them)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          float val = acc[i][j][e];
+          if (a.scale) val = val * csc[j] + csh[j];
+          if (a.relu) val = val > 0.f ? val : 0.f;
+          stf(&St[acc_row(e, lane) * SP + 32 * j + r], val);
+        }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int row = 8 * k + (lane >> 3), n = n0 + 8 * (lane & 7);
+        const int m = m0 + 32 * i + row;
+        const uint4 q = *(const uint4 *)&St[row * SP + 8 * (lane & 7)];
+        if (m < M && n < a.N) {
+          uint32_t t_, x_, b_, y_;
+          fdiv_qr((uint32_t)m, a.fw, t_, x_);
+          fdiv_qr(t_, a.fr, b_, y_);
+          const int y = a.y0 + (int)y_;
+          *(uint4 *)((bf16 *)a.dst.p + (long long)b_ * a.dst.bs + (y - a.dst.row0) * drow +
+                     (long long)x_ * a.N + n) = q;
+          if (a.mask) {
+            union {
+              uint4 u;
+              bf16 e[8];
+            } wq;
+            wq.u = q;
+            uint64_t bits = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bits |= (uint64_t)(ldf(&wq.e[e]) > 0.f ? 1 : 0) << (8 * e);
+            uint8_t *mkp = a.mask + (((long long)b_ * a.mask_h + y) * a.Wd + (int)x_) * a.N + n;
+            if (mask_vec) {
+              *(uint64_t *)mkp = bits;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) mkp[e] = (uint8_t)(bits >> (8 * e));
+            }
+          }
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+  }
+}
+
+static int conv_first_launch(ConvArgs a, int M, hipStream_t s) {
+  if (a.res.p || a.splits > 1) return (int)hipErrorInvalidValue;
+  a.fw = fast_div((uint32_t)a.Wd);
+  a.fr = fast_div((uint32_t)(a.y1 - a.y0));
+  a.fkw = fast_div((uint32_t)conv_row_vecs(a.kw, a.KC, 2));
+  const int KP = conv_row_k(a.kh, a.kw, a.KC, 2);
+  const int ny = (a.N + 63) / 64;
+  // 256-pixel tiles (64 per wave) when they fill the chip twice over, else
+  // 128-pixel ones; at most three workgroups' worth of CUs, each walking its
+  // share of the tiles, so the weights are laid out once per workgroup
+  const int t256 = (M + 255) / 256, t128 = (M + 127) / 128;
+  const bool wide = (long long)t256 * ny >= 512;
+  const int tiles = wide ? t256 : t128;
+  const int gx = std::min(tiles, std::max(1, 768 / ny));
+  const size_t lds = (size_t)64 * (KP + 8) * 2 + 4 * 32 * 72 * 2;
+  int pr = -1;
+  if (prof::on)
+    pr = prof::begin("conv_first_kernel<bf16>", 2.0 * M * a.N * a.kh * a.kw * a.KC, s,
+                     conv_bytes<bf16, false>(a, M, 1, false), 2);
+  auto go = [&](auto kernel) {
+    if (pr >= 0)
+      hipExtLaunchKernelGGL(kernel, dim3(gx, ny), dim3(256), lds, s, prof::start(pr),
+                            prof::stop(pr), 0, a, tiles, KP);
+    else
+      hipLaunchKernelGGL(kernel, dim3(gx, ny), dim3(256), lds, s, a, tiles, KP);
+  };
+  if (wide) go(conv_first_kernel<2>);
+  else go(conv_first_kernel<1>);
+  return (int)hipGetLastError();
+}
+
 template <typename T, bool DGRAD>
 static int conv_launch(const ConvArgs &a0, hipStream_t s) {
   constexpr int KR = LRCNN_CONV_KR;
@@ -839,6 +1107,10 @@ static int conv_launch(const ConvArgs &a0, hipStream_t s) {
   ConvArgs a = a0;
   const int M = a.B * (a.y1 - a.y0) * a.Wd;
   if (M <= 0 || a.N <= 0) return 0;
+  if constexpr (!DGRAD && sizeof(T) == 2) {
+    if (conv_row_packed(a.kh, a.kw, a.KC, a.N, 2, false))
+      return conv_first_launch(a, M, s);
+  }
   // (the 16-byte loaders test taps against a 64-bit mask: larger kernels
   // take the element-wise loader)
   const int es = (int)sizeof(T);
@@ -847,7 +1119,7 @@ static int conv_launch(const ConvArgs &a0, hipStream_t s) {
   a.fkw = fast_div((uint32_t)a.kw);
   // K step width of this launch (the planner counts iterations the same way)
   const int kr = conv_kr(a.kh, a.kw, a.KC, a.N, es, DGRAD);
-  const int KT = conv_k_iters(a.kh * a.kw, a.KC, es, DGRAD, kr);
+  const int KT = conv_k_iters(a.kh, a.kw, a.KC, a.N, es, DGRAD, kr);
   // a fixed split count (the layer's, for the forward) or the estimate's
   if (a.splits > 0 && !split_valid(KT, a.splits)) return (int)hipErrorInvalidValue;
   const ConvTiles ct = a.splits > 0
@@ -959,7 +1231,7 @@ static int conv_dispatch(const ConvArgs &a, hipStream_t s) {
   // single launch over all taps
   const int es = (int)sizeof(T);
   const size_t cap = a.part ? a.part_bytes : 0;
-  const double one = conv_tiles(M, a.N, conv_k_iters(a.kh * a.kw, a.KC, es, true), cap, es).us;
+  const double one = conv_tiles(M, a.N, conv_k_iters(a.kh, a.kw, a.KC, a.N, es, true), cap, es).us;
   double ph = 0;
   for (int ry = 0; ry < a.sh; ++ry)
     for (int rx = 0; rx < a.sw; ++rx) {
@@ -967,7 +1239,7 @@ static int conv_dispatch(const ConvArgs &a, hipStream_t s) {
       const PhaseDim px = phase_dim(0, a.Wd, a.pw, a.kw, a.sw, rx);
       if (py.count == 0 || px.count == 0 || (py.taps * px.taps == 0 && !a.dst_init)) continue;
       ph += 5.0 + conv_tiles((long long)a.B * py.count * px.count, a.N,
-                             conv_k_iters(py.taps * px.taps, a.KC, es, true), cap, es).us;
+                             conv_k_iters(py.taps, px.taps, a.KC, a.N, es, true), cap, es).us;
     }
   if (ph >= one && g_phases != 1) return conv_launch<T, DGRAD>(a, s);
   for (int ry = 0; ry < a.sh; ++ry)

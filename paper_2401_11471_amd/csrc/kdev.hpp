@@ -313,6 +313,15 @@ __device__ __forceinline__ uint4 load16z(const void *base, long long off_bytes, 
   const uint4 *q = ok ? (const uint4 *)((const char *)base + off_bytes) : &g_zero16[0];
   return *q;
 }
+// Three float32 (12 bytes, 4-byte aligned) and a zero, or zeros if !ok, in
+// one branch-free load.
+template <typename T>
+__device__ __forceinline__ uint4 load12(const T *p, bool ok) {
+  typedef uint32_t u32x3 __attribute__((ext_vector_type(3), aligned(4)));
+  typedef __attribute__((address_space(1))) const u32x3 g_u32x3;
+  const u32x3 v = *(g_u32x3 *)(ok ? (const void *)p : (const void *)&g_zero16[0]);
+  return make_uint4(v.x, v.y, v.z, 0);
+}
 // 16 bytes at p (or, if !ok, the zero block at `zero`, whose address the
 // caller holds in registers) copied from global memory straight into LDS
 // (global_load_lds_dwordx4): lane l of the wave writes bytes

@@ -120,7 +120,7 @@ struct ConvArgs {
   // forward with KC channels in one vector: each K iteration covers KR taps,
   // one per 16-byte vector of a tile row (set by the launcher)
   int tpack;
-  FastDiv fkw;  // division by kw
+  FastDiv fkw;  // division by kw (row-packed: by the vectors of a kernel row)
   // input gradient of a strided convolution split into phases (pst > 1,
   // set by the launcher): this launch covers the producer pixels
   // y = y0 + pst * yy (yy < y1 - y0), x = px0 + pst * xx (xx < Wd), which
@@ -279,10 +279,26 @@ inline ConvTiles conv_tiles_split(long long M, int N, int KT, int s, int es,
 // iteration covers kr 16-byte vectors of a tile row (LRCNN_CONV_KR, or
 // LRCNN_CONV_KR_WIN for the bfloat16 forward of a windowed kernel whose
 // channels fill whole vectors: twice the MFMAs per K step there).
-// A forward convolution whose input channels fit in one 16-byte vector
-// (kc * es < 16, e.g. a 3-channel image) packs LRCNN_CONV_KR taps into one
-// iteration instead (tap_packed).
+// A forward convolution whose input channels do not fill one 16-byte vector
+// (kc * es < 16, e.g. a 3-channel image) packs its K vectors instead of
+// giving each tap a channel block of its own: one tap per vector,
+// LRCNN_CONV_KR taps per iteration (conv_tap_packed), or, in bfloat16 with
+// whole output vectors, the kw * kc contiguous elements of a kernel row as
+// ceil(kw * kc / 8) vectors (conv_row_packed): 21 elements in 3 vectors for a
+// 7-wide kernel over 3 channels, where one tap per vector takes 7. (In
+// float32 a 3 x 3 kernel over 3 channels needs 9 vectors either way.) Its
+// kernel holds a 64-output weight tile in LDS, so K is limited; it runs
+// unsplit.
 inline bool conv_tap_packed(int kc, int es, bool dgrad) { return !dgrad && kc * es < 16; }
+inline int conv_row_vecs(int kw, int kc, int es) { return (kw * kc * es + 15) / 16; }
+// K of a row-packed convolution in whole 16-element slices
+inline int conv_row_k(int kh, int kw, int kc, int es) {
+  return (kh * conv_row_vecs(kw, kc, es) + 1) / 2 * 16;
+}
+inline bool conv_row_packed(int kh, int kw, int kc, int n, int es, bool dgrad) {
+  return es == 2 && conv_tap_packed(kc, es, dgrad) && n % 8 == 0 && kh <= 64 && kw <= 64 &&
+         conv_row_k(kh, kw, kc, es) <= 320;
+}
 // the 16-byte loaders (taps tested against a 64-bit mask)
 inline bool conv_vec(int kh, int kw, int kc, int n, int es, bool dgrad) {
   const int E = 16 / es;
@@ -293,11 +309,12 @@ inline int conv_kr(int kh, int kw, int kc, int n, int es, bool dgrad) {
              ? LRCNN_CONV_KR_WIN
              : LRCNN_CONV_KR;
 }
-inline int conv_k_iters(int taps, int kc, int es, bool dgrad = false,
+inline int conv_k_iters(int kh, int kw, int kc, int n, int es, bool dgrad = false,
                         int kr = LRCNN_CONV_KR) {
-  if (conv_tap_packed(kc, es, dgrad)) return (taps + LRCNN_CONV_KR - 1) / LRCNN_CONV_KR;
+  if (conv_row_packed(kh, kw, kc, n, es, dgrad)) return 1;  // never split
+  if (conv_tap_packed(kc, es, dgrad)) return (kh * kw + LRCNN_CONV_KR - 1) / LRCNN_CONV_KR;
   const int bk = 16 * kr / es;
-  return taps * ((kc + bk - 1) / bk);
+  return kh * kw * ((kc + bk - 1) / bk);
 }
 
 struct WgradArgs {

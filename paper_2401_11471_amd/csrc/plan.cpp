@@ -351,7 +351,7 @@ static void forward_splits(Plan &P,
     if (d.op != LRCNN_OP_CONV) continue;
     const Shape &su = P.shp[d.in0], &sv = P.shp[v];
     const int kr = conv_kr(d.kh, d.kw, su.c, sv.c, P.es, false);
-    const int KT = conv_k_iters(d.kh * d.kw, su.c, P.es, false, kr);
+    const int KT = conv_k_iters(d.kh, d.kw, su.c, sv.c, P.es, false, kr);
     std::vector<long long> ms;
     long long mmax = 0;
     for (auto *tab : tabs)
@@ -479,14 +479,16 @@ static void layout(Plan &P, Layout &L, const Fuse &F, const std::vector<int> &ca
         const int u0 = std::max(0, q.a * d.sh - d.ph);
         const int u1 = std::min(su.h, (q.b - 1) * d.sh - d.ph + d.kh);
         if (padded) xrows = std::max(xrows, u1 - u0);
-        // input gradient: over the rows the windows reach, or over the whole
-        // error window when the launch initializes it
-        for (const int rows_ : {u1 - u0, bwd_covers(u0, u1, qu.lo, qu.hi) ? qu.hi - qu.lo : 0}) {
+        // input gradient: over the whole error window when the launch
+        // initializes it (a single consumer's always does if it may), else
+        // over the rows the windows reach
+        const int ext = bwd_covers(u0, u1, qu.lo, qu.hi) ? qu.hi - qu.lo : u1 - u0;
+        for (int rows_ = ext;; rows_ = u1 - u0) {
           const long long md = (long long)P.cfg.batch * rows_ * su.w;
-          if (md <= 0) continue;
           const int sd =
-              conv_split_count(md, su.c, conv_k_iters(taps, sv.c, P.es, true), pcap, P.es);
+              conv_split_count(md, su.c, conv_k_iters(d.kh, d.kw, sv.c, su.c, P.es, true), pcap, P.es);
           if (sd > 1) part = std::max(part, (size_t)(sd * md * su.c * 4));
+          if (rows_ == u1 - u0 || P.cons[d.in0].size() == 1) break;
         }
       }
     }
