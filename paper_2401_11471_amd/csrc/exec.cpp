@@ -36,8 +36,8 @@ thread_local bool g_serial_wg = false;
 
 // The weight gradient of a convolution does not depend on the input
 // gradient of the same layer, and a band's launches of either are often too
-// small to fill the GPU, so the backward runs the weight gradients on a side
-// stream beside the caller's stream. Events order them: the side stream
+// small to fill the GPU, so the backward runs the longer weight gradients on
+// a side stream beside the caller's stream. Events order them: the side stream
 // waits until the error operand is formed; the caller's stream waits for the
 // last weight gradient before the error-operand buffer is formed again and
 // at the end of every band (the next band's recompute overwrites the
@@ -600,7 +600,7 @@ struct Run {
       g.kh = d.kh, g.kw = d.kw, g.sh = d.sh, g.sw = d.sw, g.ph = d.ph, g.pw = d.pw;
       g.overwrite = dw_set[v] ? 0 : 1;
       dw_set[v] = 1;
-      if (side) {
+      if (side && fork_wgrad(v, a, b, u != 0 || want_dx)) {
         LAUNCH(hipEventRecord((hipEvent_t)P.ev_act, (hipStream_t)stream), "event record");
         LAUNCH(hipStreamWaitEvent(side, (hipEvent_t)P.ev_act, 0), "stream wait");
         LAUNCH(launch_wgrad(dt, g, wdst, side), "weight gradient");
@@ -739,6 +739,26 @@ struct Run {
              "add backward");
     }
     return LRCNN_OK;
+  }
+
+  // Whether conv v's weight gradient over rows [a, b) goes to the side
+  // stream. A fork and its join cost the two queues about 10 us a conv, so it
+  // pays where an input gradient runs beside it (dgrad) and the weight
+  // gradient itself takes that long (estimated at 400 / 90 TFLOP/s and
+  // 4 TB/s). Per step, always forked -> by this rule, launched from the host:
+  // 224-pixel ResNet-50 16.4 -> 13.6 ms, block 2 at 28 x 28 layer-wise 160 ->
+  // 129 us, the tiny net 692 -> 545 us, ResNet-50's first block at 600 x 900
+  // 16.9 -> 15.7 ms, block 3 14.3 -> 13.1; as a replayed graph, where a join
+  // is cheaper, 224-pixel ResNet-50 13.1 -> 13.8 ms and 2400 x 3600 209 ->
+  // 212. From 40 us on the overlap of VGG-16 and block 4 is lost as well.
+  bool fork_wgrad(int v, int a, int b, bool dgrad) const {
+    if (!dgrad) return false;
+    const lrcnn_node &d = P.nodes[v];
+    const Shape &sv = P.shp[v], &su = P.shp[d.in0];
+    const double px = (double)P.cfg.batch * (b - a) * sv.w;
+    const double flops = 2.0 * px * sv.c * d.kh * d.kw * su.c;
+    const double bytes = px * (sv.c + (double)d.sh * d.sw * su.c) * P.es;
+    return std::max(flops / (P.es == 2 ? 400e6 : 90e6), bytes / 4e6) >= 10.0;
   }
 
   // a conv whose error operand the add's backward writes (no error window)
