@@ -128,6 +128,29 @@ int launch_conv(int dt, int dgrad, const ConvArgs &a, void *stream) {
 }
 
 // ------------------------------------------------------------- max-pool
+// V argmax bytes in as few stores as the address allows (`wide`: p is a
+// multiple of V bytes from a V-aligned base)
+template <int V>
+__device__ __forceinline__ void st_arg(uint8_t *p, const int (&m)[V], bool wide) {
+  if constexpr (V == 1) {
+    *p = (uint8_t)m[0];
+  } else if (wide) {
+    uint32_t w[V / 4];
+#pragma unroll
+    for (int i = 0; i < V / 4; ++i)
+      w[i] = (uint32_t)m[4 * i] | ((uint32_t)m[4 * i + 1] << 8) | ((uint32_t)m[4 * i + 2] << 16) |
+             ((uint32_t)m[4 * i + 3] << 24);
+    if constexpr (V == 8) *(uint2 *)p = make_uint2(w[0], w[1]);
+    else *(uint32_t *)p = w[0];
+  } else {
+#pragma unroll
+    for (int e = 0; e < V; ++e) p[e] = (uint8_t)m[e];
+  }
+}
+
+// HBM-bound: each source row is read by one or two output rows (the second
+// time from L2), 16 bytes per load in bfloat16, and the argmax leaves in one
+// store per thread.
 template <typename T, int V>
 __global__ void pool_fwd_kernel(PoolArgs a) {
   const int R = a.y1 - a.y0;
@@ -136,6 +159,8 @@ __global__ void pool_fwd_kernel(PoolArgs a) {
   const long long srow = (long long)a.src.W * a.src.C;
   const long long drow = (long long)a.Wd * a.C;
   const bool fast = total < (1ll << 32);
+  const bool am_wide = ((uintptr_t)a.am & (V - 1)) == 0;
+  const bool mask_wide = ((uintptr_t)a.mask & (V - 1)) == 0;
   GRID_STRIDE(idx, total) {
     int c, x, yy, b;
     if (fast) {
@@ -154,13 +179,15 @@ __global__ void pool_fwd_kernel(PoolArgs a) {
     }
     const int y = a.y0 + yy;
     const T *src = (const T *)a.src.p + b * a.src.bs;
-    float best[4];
-    int bi[4] = {0, 0, 0, 0};
+    float best[V];
+    int bi[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) bi[e] = 0;
     for (int i = 0; i < a.kh; ++i) {
       const int sy = y * a.sh - a.ph + i;
       for (int j = 0; j < a.kw; ++j) {
         const int sx = x * a.sw - a.pw + j;
-        float v[4];
+        float v[V];
         if (sy >= 0 && sy < a.Hs && sx >= 0 && sx < a.Ws) {
           ldv<T, V>(src + (sy - a.src.row0) * srow + (long long)sx * a.src.C + c, v);
         } else {
@@ -180,32 +207,31 @@ __global__ void pool_fwd_kernel(PoolArgs a) {
     stv<T, V>((T *)a.dst.p + o, best);
     const long long flat = (((long long)b * R + yy) * a.Wd + x) * a.C + c;
     const long long mfl = (((long long)b * a.mask_h + y) * a.Wd + x) * a.C + c;
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      if (a.am) a.am[flat + e] = (uint8_t)bi[e];
-      if (a.mask) a.mask[mfl + e] = (uint8_t)bi[e];
-    }
+    if (a.am) st_arg<V>(a.am + flat, bi, am_wide);
+    if (a.mask) st_arg<V>(a.mask + mfl, bi, mask_wide);
   }
 }
 
+template <typename T>
+static void pool_fwd_go(const PoolArgs &a, int V, unsigned g, hipStream_t s) {
+  if (V == 8) pool_fwd_kernel<T, 8><<<g, 256, 0, s>>>(a);
+  else if (V == 4) pool_fwd_kernel<T, 4><<<g, 256, 0, s>>>(a);
+  else pool_fwd_kernel<T, 1><<<g, 256, 0, s>>>(a);
+}
 
 int launch_pool_fwd(int dt, const PoolArgs &a0, void *stream) {
   const long long total = (long long)a0.B * (a0.y1 - a0.y0) * a0.Wd * a0.C;
   if (total <= 0) return 0;
   hipStream_t s = (hipStream_t)stream;
-  const bool v4 = a0.C % 4 == 0;
+  // whole 16-byte storage vectors per thread when the channels fill them
+  const int V = dt == DT_BF16 && a0.C % 8 == 0 ? 8 : a0.C % 4 == 0 ? 4 : 1;
   PoolArgs a = a0;
-  a.fcv = fast_div((uint32_t)(v4 ? a.C / 4 : a.C));
+  a.fcv = fast_div((uint32_t)(a.C / V));
   a.fw = fast_div((uint32_t)a.Wd);
   a.fr = fast_div((uint32_t)(a.y1 - a.y0));
-  const unsigned g = grid_for(v4 ? total / 4 : total);
-  if (dt == DT_F32) {
-    if (v4) pool_fwd_kernel<float, 4><<<g, 256, 0, s>>>(a);
-    else pool_fwd_kernel<float, 1><<<g, 256, 0, s>>>(a);
-  } else {
-    if (v4) pool_fwd_kernel<bf16, 4><<<g, 256, 0, s>>>(a);
-    else pool_fwd_kernel<bf16, 1><<<g, 256, 0, s>>>(a);
-  }
+  const unsigned g = grid_for(total / V);
+  if (dt == DT_F32) pool_fwd_go<float>(a, V, g, s);
+  else pool_fwd_go<bf16>(a, V, g, s);
   return (int)hipGetLastError();
 }
 
