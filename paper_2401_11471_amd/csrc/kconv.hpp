@@ -17,14 +17,17 @@ extern thread_local int g_phases;
 // ONE: a single tap (1x1 kernel, or a phase with one tap): each A row's
 // validity and address are fixed for the launch, so a K step only adds the
 // channel offset.
-template <typename T, int BN, int KR, bool DGRAD, bool VEC, bool S1, bool ONE = false>
+// BMT: pixels of a tile (64 or 128).
+template <typename T, int BN, int KR, bool DGRAD, bool VEC, bool S1, bool ONE = false,
+          int BMT = 128>
 // bfloat16: three workgroups per CU (the register budget is set for it;
 // the swizzled LDS tiles fit three); float32 keeps the registers of two
 __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(ConvArgs a) {
   using CF = Cfg<T, KR>;
   constexpr int E = CF::E, BK = CF::BK, LDK = CF::LDK;
+  constexpr int BM = BMT, MB = BM / 64;
   constexpr int NB = BN / 64;
-  constexpr int NA = KR / 2;             // A rows loaded per thread
+  constexpr int NA = BM * KR / 256;      // A rows loaded per thread
   constexpr int NBL = BN * KR / 256;     // B vectors loaded per thread
   constexpr int RS = 256 / KR;           // row stride between a thread's loads
   // forward with 16-byte rows: both operands copied straight from global
@@ -380,15 +383,15 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
     }
   };
 
-  f32x16 acc[2][NB];
+  f32x16 acc[MB][NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int wm = (wave & 1) * 64, wn = (wave >> 1) * (BN / 2);
+  const int wm = (wave & 1) * (BM / 2), wn = (wave >> 1) * (BN / 2);
   auto store = [&](int st) {
 #pragma unroll
     for (int i = 0; i < NA; ++i)
@@ -412,7 +415,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
     }
   };
   const int n = kend - kbeg;
-  using FR = Frag<T, BN, KR, 0, BKM>;
+  using FR = Frag<T, BN, KR, 0, BKM, BM, BN, MB>;
   FR f0, f1;
   int t = 0;
   if constexpr (DMA) {
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
     float *part = a.part + (long long)tl.z * M * a.N;
     const int col = lane & 31;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int m = m0 + wm + 32 * i + acc_row(v, lane);
@@ -558,7 +561,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
     // the unrolled loop has no branches)
     auto stage = [&](auto SC, auto RL, int h0) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int r = wm - h0 + 32 * i + acc_row(v, lane);
@@ -655,7 +658,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
     if (h0) __syncthreads();
     if (wm >= h0 && wm < h0 + HR) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int r = wm - h0 + 32 * i + acc_row(v, lane);
@@ -683,7 +686,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
     return;
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < MB; ++i) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int m = m0 + wm + 32 * i + acc_row(v, lane);
@@ -1069,6 +1072,7 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
   }
 }
 
+template <typename T>
 static int conv_first_launch(ConvArgs a, int M, hipStream_t s) {
   if (a.res.p || a.splits > 1) return (int)hipErrorInvalidValue;
   a.fw = fast_div((uint32_t)a.Wd);
@@ -1087,7 +1091,7 @@ static int conv_first_launch(ConvArgs a, int M, hipStream_t s) {
   int pr = -1;
   if (prof::on)
     pr = prof::begin("conv_first_kernel<bf16>", 2.0 * M * a.N * a.kh * a.kw * a.KC, s,
-                     conv_bytes<bf16, false>(a, M, 1, false), 2);
+                     conv_bytes<T, false>(a, M, 1, false), 2);
   auto go = [&](auto kernel) {
     if (pr >= 0)
       hipExtLaunchKernelGGL(kernel, dim3(gx, ny), dim3(256), lds, s, prof::start(pr),
@@ -1109,7 +1113,7 @@ static int conv_launch(const ConvArgs &a0, hipStream_t s) {
   if (M <= 0 || a.N <= 0) return 0;
   if constexpr (!DGRAD && sizeof(T) == 2) {
     if (conv_row_packed(a.kh, a.kw, a.KC, a.N, 2, false))
-      return conv_first_launch(a, M, s);
+      return conv_first_launch<T>(a, M, s);
   }
   // (the 16-byte loaders test taps against a 64-bit mask: larger kernels
   // take the element-wise loader)
@@ -1117,14 +1121,18 @@ static int conv_launch(const ConvArgs &a0, hipStream_t s) {
   const bool vec = conv_vec(a.kh, a.kw, a.KC, a.N, es, DGRAD);
   a.tpack = !vec && conv_tap_packed(a.KC, es, DGRAD);
   a.fkw = fast_div((uint32_t)a.kw);
-  // K step width of this launch (the planner counts iterations the same way)
+  // the input gradient of a strided convolution divides by the stride
+  // (a phase of it is dense)
+  const bool s1 = !DGRAD || (a.sh == 1 && a.sw == 1) || a.pst > 1;
+  // K step width of this launch (the planner counts iterations the same
+  // way), a fixed split count (the layer's, for the forward) or the estimate's
+  const size_t cap = a.part ? a.part_bytes : 0;
   const int kr = conv_kr(a.kh, a.kw, a.KC, a.N, es, DGRAD);
   const int KT = conv_k_iters(a.kh, a.kw, a.KC, a.N, es, DGRAD, kr);
-  // a fixed split count (the layer's, for the forward) or the estimate's
   if (a.splits > 0 && !split_valid(KT, a.splits)) return (int)hipErrorInvalidValue;
   const ConvTiles ct = a.splits > 0
-                           ? conv_tiles_split(M, a.N, KT, a.splits, es, kr)
-                           : conv_tiles(M, a.N, KT, a.part ? a.part_bytes : 0, es, kr);
+                           ? conv_tiles_split(M, a.N, KT, a.splits, es, kr, vec)
+                           : conv_tiles(M, a.N, KT, cap, es, kr, DGRAD, vec && s1);
   const int bn = ct.bn;
   const int splits = ct.splits;
   // a fused residual add needs the vector epilogues of the forward
@@ -1135,7 +1143,7 @@ static int conv_launch(const ConvArgs &a0, hipStream_t s) {
   a.fr = fast_div((uint32_t)(a.y1 - a.y0));
   a.fn = fast_div((uint32_t)a.N);
   a.kts = (KT + splits - 1) / splits;
-  dim3 grid((M + BM - 1) / BM, (a.N + bn - 1) / bn, splits);
+  dim3 grid((M + ct.bm - 1) / ct.bm, (a.N + bn - 1) / bn, splits);
   int pr = -1;
   if (prof::on) {
     // algorithmic FLOPs: forward 2*M*N*K; input gradient 2 * consumer pixels
@@ -1151,26 +1159,34 @@ static int conv_launch(const ConvArgs &a0, hipStream_t s) {
                      (!vec ? ", scalar>" : one_ ? ", 1x1>" : ", vec>");
     pr = prof::begin(nm, fl, s, conv_bytes<T, DGRAD>(a, M, splits, false), es);
   }
-  // the input gradient of a strided convolution divides by the stride
-  // (a phase of it is dense)
-  const bool s1 = !DGRAD || (a.sh == 1 && a.sw == 1) || a.pst > 1;
-  const bool one = vec && s1 && a.kh == 1 && a.kw == 1;
+  // (a bfloat16 1x1 input gradient runs the windowed kernel with its one tap:
+  // both operands are copied straight to LDS there, 22.5 -> 20.9 us for 256
+  // channels into 64 at 136800 pixels)
+  constexpr bool ONE = !(DGRAD && sizeof(T) == 2 && LRCNN_DG_DMA);
+  const bool one = ONE && vec && s1 && a.kh == 1 && a.kw == 1;
   bool done = false;
   if constexpr (!DGRAD && sizeof(T) == 2 && LRCNN_CONV_KR_WIN != KR) {
     // bfloat16 forward of a windowed kernel: wider K steps, 64-wide tiles
     if (kr != KR) {
       if (bn != 64 || !vec || one) return (int)hipErrorInvalidValue;
-      launch_timed(conv_gemm_kernel<T, 64, LRCNN_CONV_KR_WIN, false, true, true>, grid, s, pr, a);
+      if (ct.bm == 64)
+        launch_timed(conv_gemm_kernel<T, 64, LRCNN_CONV_KR_WIN, false, true, true, false, 64>, grid,
+                     s, pr, a);
+      else
+        launch_timed(conv_gemm_kernel<T, 64, LRCNN_CONV_KR_WIN, false, true, true>, grid, s, pr, a);
       done = true;
     }
   }
   if (done) {
+  } else if (ct.bm == 64) {
+    if (one) launch_timed(conv_gemm_kernel<T, 64, KR, DGRAD, true, true, ONE, 64>, grid, s, pr, a);
+    else launch_timed(conv_gemm_kernel<T, 64, KR, DGRAD, true, true, false, 64>, grid, s, pr, a);
   } else if (bn == 64) {
     if (!s1) {
       if (vec) launch_timed(conv_gemm_kernel<T, 64, KR, DGRAD, true, false>, grid, s, pr, a);
       else launch_timed(conv_gemm_kernel<T, 64, KR, DGRAD, false, false>, grid, s, pr, a);
     } else if (one) {
-      launch_timed(conv_gemm_kernel<T, 64, KR, DGRAD, true, true, true>, grid, s, pr, a);
+      launch_timed(conv_gemm_kernel<T, 64, KR, DGRAD, true, true, ONE>, grid, s, pr, a);
     } else if (vec) {
       launch_timed(conv_gemm_kernel<T, 64, KR, DGRAD, true, true>, grid, s, pr, a);
     } else {
@@ -1181,7 +1197,7 @@ static int conv_launch(const ConvArgs &a0, hipStream_t s) {
       if (vec) launch_timed(conv_gemm_kernel<T, 128, KR, DGRAD, true, false>, grid, s, pr, a);
       else launch_timed(conv_gemm_kernel<T, 128, KR, DGRAD, false, false>, grid, s, pr, a);
     } else if (one) {
-      launch_timed(conv_gemm_kernel<T, 128, KR, DGRAD, true, true, true>, grid, s, pr, a);
+      launch_timed(conv_gemm_kernel<T, 128, KR, DGRAD, true, true, ONE>, grid, s, pr, a);
     } else if (vec) {
       launch_timed(conv_gemm_kernel<T, 128, KR, DGRAD, true, true>, grid, s, pr, a);
     } else {
@@ -1231,15 +1247,15 @@ static int conv_dispatch(const ConvArgs &a, hipStream_t s) {
   // single launch over all taps
   const int es = (int)sizeof(T);
   const size_t cap = a.part ? a.part_bytes : 0;
-  const double one = conv_tiles(M, a.N, conv_k_iters(a.kh, a.kw, a.KC, a.N, es, true), cap, es).us;
+  const double one = conv_dgrad_tiles(M, a.N, a.kh, a.kw, a.KC, cap, es, false).us;
   double ph = 0;
   for (int ry = 0; ry < a.sh; ++ry)
     for (int rx = 0; rx < a.sw; ++rx) {
       const PhaseDim py = phase_dim(a.y0, a.y1, a.ph, a.kh, a.sh, ry);
       const PhaseDim px = phase_dim(0, a.Wd, a.pw, a.kw, a.sw, rx);
       if (py.count == 0 || px.count == 0 || (py.taps * px.taps == 0 && !a.dst_init)) continue;
-      ph += 5.0 + conv_tiles((long long)a.B * py.count * px.count, a.N,
-                             conv_k_iters(py.taps, px.taps, a.KC, a.N, es, true), cap, es).us;
+      ph += 5.0 + conv_dgrad_tiles((long long)a.B * py.count * px.count, a.N, py.taps, px.taps,
+                                   a.KC, cap, es, true).us;
     }
   if (ph >= one && g_phases != 1) return conv_launch<T, DGRAD>(a, s);
   for (int ry = 0; ry < a.sh; ++ry)

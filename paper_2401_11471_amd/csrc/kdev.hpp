@@ -146,24 +146,26 @@ struct KM {
 // (the input gradient's weights, both weight-gradient operands) be stored
 // with 16-byte writes.
 // TA / TB: rows of the A tile and columns of the B tile in LDS (the row
-// width of a k-major operand); NB = BN / 64 column blocks per wave.
-template <typename T, int BN, int KR, int AKM = 0, int BKM = 0, int TA = BM, int TB = BN>
+// width of a k-major operand); MB row blocks and NB = BN / 64 column blocks
+// per wave.
+template <typename T, int BN, int KR, int AKM = 0, int BKM = 0, int TA = BM, int TB = BN,
+          int MB = 2>
 struct Frag;
 
-template <int BN, int KR, int AKM, int BKM, int TA, int TB>
-struct Frag<float, BN, KR, AKM, BKM, TA, TB> {
+template <int BN, int KR, int AKM, int BKM, int TA, int TB, int MB>
+struct Frag<float, BN, KR, AKM, BKM, TA, TB, MB> {
   static constexpr int LDK = Cfg<float, KR>::LDK, NB = BN / 64, NV = KR / 2;
   static constexpr int S = 4 * NV;            // K elements per lane group
   static constexpr int PA = KM<float, TA>::P, PB = KM<float, TB>::P;
   // instructions per tile step: MFMAs and LDS reads of one fragment load
-  static constexpr int NMFMA = S * 2 * NB;
-  static constexpr int NDSR = (AKM ? 2 * S : 2 * NV) + (BKM ? NB * S : NB * NV);
-  float a[2][S], b[NB][S];
+  static constexpr int NMFMA = S * MB * NB;
+  static constexpr int NDSR = (AKM ? MB * S : MB * NV) + (BKM ? NB * S : NB * NV);
+  float a[MB][S], b[NB][S];
   __device__ __forceinline__ void load(const float *As, const float *Bs, int wm, int wn,
                                        int lane) {
     const int r = lane & 31, g = lane >> 5;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < MB; ++i) {
       if (AKM) {
 #pragma unroll
         for (int s = 0; s < S; ++s) a[i][s] = As[(S * g + s) * PA + wm + 32 * i + r];
@@ -193,11 +195,11 @@ struct Frag<float, BN, KR, AKM, BKM, TA, TB> {
       }
     }
   }
-  __device__ __forceinline__ void mma(f32x16 (&acc)[2][NB]) const {
+  __device__ __forceinline__ void mma(f32x16 (&acc)[MB][NB]) const {
 #pragma unroll
     for (int s = 0; s < S; ++s)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
@@ -230,17 +232,17 @@ __device__ __forceinline__ bf16x8 ld_tr8(const bf16 *T, int base, int s, int lan
   return __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-template <int BN, int KR, int AKM, int BKM, int TA, int TB>
-struct Frag<bf16, BN, KR, AKM, BKM, TA, TB> {
+template <int BN, int KR, int AKM, int BKM, int TA, int TB, int MB>
+struct Frag<bf16, BN, KR, AKM, BKM, TA, TB, MB> {
   static constexpr int LDK = Cfg<bf16, KR>::LDK, NB = BN / 64, NV = KR / 2;
-  static constexpr int NMFMA = NV * 2 * NB;
-  static constexpr int NDSR = (AKM ? 4 * NV : 2 * NV) + (BKM ? 2 * NB * NV : NB * NV);
-  bf16x8 a[2][NV], b[NB][NV];
+  static constexpr int NMFMA = NV * MB * NB;
+  static constexpr int NDSR = (AKM ? 2 * MB * NV : MB * NV) + (BKM ? 2 * NB * NV : NB * NV);
+  bf16x8 a[MB][NV], b[NB][NV];
   __device__ __forceinline__ void load(const bf16 *As, const bf16 *Bs, int wm, int wn,
                                        int lane) {
     const int r = lane & 31, g = lane >> 5;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < MB; ++i) {
       if (AKM) {
 #pragma unroll
         for (int q = 0; q < NV; ++q) a[i][q] = ld_tr8<TA, NV>(As, wm + 32 * i, q, lane);
@@ -264,11 +266,11 @@ struct Frag<bf16, BN, KR, AKM, BKM, TA, TB> {
       }
     }
   }
-  __device__ __forceinline__ void mma(f32x16 (&acc)[2][NB]) const {
+  __device__ __forceinline__ void mma(f32x16 (&acc)[MB][NB]) const {
 #pragma unroll
     for (int s = 0; s < NV; ++s)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][s], b[j][s], acc[i][j],

@@ -3,6 +3,7 @@
 // launch as an int (0 = success).
 #pragma once
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 
@@ -180,6 +181,9 @@ struct SplitCost {
   double fixed_us;  // per-launch fixed cost
   int max_s = 128;  // largest split count considered
   double share = LRCNN_SHARE2;  // time factor of a workgroup sharing its CU
+  double lat_us = 0;            // least time of one iteration, however few workgroups
+  double split_us = 6.0;        // a split's extra launch
+  double part_rate = 1.5e7;     // partial sums written and read back, bytes per us
 };
 struct SplitChoice {
   int s;
@@ -192,8 +196,8 @@ inline double split_cost(long long tiles, int KT, long long part_elems, const Sp
   const long long per_cu = (wg + 255) / 256;
   const long long kts = (KT + s - 1) / s;
   const double share = per_cu >= 2 && c.occ >= 2 ? c.share : 1.0;
-  double t = (double)kts * (double)per_cu * c.step_us * share + c.fixed_us;
-  if (s > 1) t += 6.0 + (double)s * (double)part_elems * 8.0 / 1.5e7;
+  double t = (double)kts * std::max(c.lat_us, (double)per_cu * c.step_us * share) + c.fixed_us;
+  if (s > 1) t += c.split_us + (double)s * (double)part_elems * 8.0 / c.part_rate;
   return t;
 }
 // A split count s of a K loop of KT iterations is used only when no smaller
@@ -235,45 +239,82 @@ inline int split_count(long long tiles, int KT, long long part_elems, size_t cap
 }
 // Tile width and split count of a convolution launch (forward or input
 // gradient, M x N outputs, KT K iterations): 128-row tiles, 64 or 128
-// columns wide. Narrow tiles double the workgroup count of a launch, which
-// fills the CUs better when a band gives only a few hundred 128 x 128
-// tiles; the cheaper of the two estimates is taken.
+// columns wide, or 64 x 64 (dense 16-byte loaders only). Narrow tiles double
+// the workgroup count of a launch, which fills the CUs better when a band
+// gives only a few hundred 128 x 128 tiles; small ones double it again where
+// even those leave CUs idle. The cheapest estimate is taken. An output
+// element sums K alike in all of them.
 struct ConvTiles {
   int bn, splits;
   double us;  // estimated duration
+  int bm = 128;
 };
-// (kr: 16-byte vectors per K iteration; an iteration of 8 costs about twice
-// one of 4, and its 72 KiB LDS ring fits two 64-wide workgroups per CU;
-// 8-vector launches use 64-wide tiles only)
+// Cost of a launch with bm x bn tiles and kr 16-byte vectors per K
+// iteration. bfloat16 is bound by what an iteration moves into and out of
+// LDS, so workgroups that share a CU add up, and a lone one cannot go below
+// its chain of copy, barrier and LDS reads. us per iteration, shared / lone:
+//   128 x 64   4 vectors 0.19 / 0.25 (input gradient 0.19 / 0.27), 8 vectors
+//              0.28 / 0.39
+//   128 x 128  4 vectors 0.36 / 0.29
+//   64 x 64    4 vectors 0.135 / 0.17 (input gradient 0.23), 8 vectors 0.19 /
+//              0.295
+// and a split adds its epilogue launch and the partial sums' way to memory
+// and back. Measured on the layers of ResNet-50 with operands outside the
+// L2s: 2048 channels into 512 over 1808 pixels 20.1 us in 128 x 64 tiles, 16.1
+// in 64 x 64, 19.5 split in two; 1024 into 256 over 3136 pixels 11.6, 9.5 and
+// 14.4; 3 x 3 of 256 into 512 over 6272 pixels, two tiles per CU, 27.5 and
+// 34.2. In float32 (matrix-core bound) small tiles even out the last round:
+// 3 x 3 of 256 channels over 34200 pixels 380 -> 359 us.
+inline SplitCost conv_cost(int bn, int es, int kr, bool dgrad, int bm = 128) {
+  if (es != 2) {
+    if (bm == 64) return SplitCost{0.41 * kr / 4.0, 4, 4.5};
+    return SplitCost{(bn == 64 ? LRCNN_STEP_N64 : LRCNN_STEP_N128) * kr / 4.0,
+                     bn == 64 && kr <= 4 ? 3 : 2, 5.0};
+  }
+  const bool m = bm == 64, wide = kr > 4;
+  const double thr = m ? (wide ? 0.19 : 0.135) : wide ? 0.28 : bn == 64 ? 0.19 : 0.36;
+  const double lat = wide ? (m ? 0.295 : 0.39)
+                     : dgrad ? (m ? 0.23 : bn == 64 ? 0.27 : 0.29)
+                             : (m ? 0.17 : bn == 64 ? 0.25 : 0.29);
+  return SplitCost{thr, wide && !m ? 2 : 3, m ? 4.2 : 4.5, 128, 1.0, lat, 2.0, 3.8e6};
+}
+// (8-vector launches use 64-wide tiles only)
 inline ConvTiles conv_tiles(long long M, int N, int KT, size_t cap, int es,
-                            int kr = LRCNN_CONV_KR) {
-  const double f = (es == 2 ? 0.75 : 1.0) * kr / 4.0;
-  const long long mt = (M + 127) / 128;
-  SplitChoice n64 = split_choice(mt * ((N + 63) / 64), KT, M * (long long)N, cap,
-                                 SplitCost{LRCNN_STEP_N64 * f, kr > 4 ? 2 : 3, 5.0});
-  if (N <= 64 || kr > 4) return ConvTiles{64, n64.s, n64.us};
-  SplitChoice n128 = split_choice(mt * ((N + 127) / 128), KT, M * (long long)N, cap,
-                                  SplitCost{LRCNN_STEP_N128 * f, 2, 5.0});
-  return n64.us < n128.us * LRCNN_NARROW_GAIN ? ConvTiles{64, n64.s, n64.us}
-                                              : ConvTiles{128, n128.s, n128.us};
+                            int kr = LRCNN_CONV_KR, bool dgrad = false, bool small = false) {
+  const long long mt = (M + 127) / 128, pe = M * (long long)N;
+  const SplitChoice n64 = split_choice(mt * ((N + 63) / 64), KT, pe, cap,
+                                       conv_cost(64, es, kr, dgrad));
+  ConvTiles best{64, n64.s, n64.us, 128};
+  if (N > 64 && kr <= 4) {
+    const SplitChoice n128 = split_choice(mt * ((N + 127) / 128), KT, pe, cap,
+                                          conv_cost(128, es, kr, dgrad));
+    if (!(n64.us < n128.us * LRCNN_NARROW_GAIN)) best = ConvTiles{128, n128.s, n128.us, 128};
+  }
+  if (small) {
+    const SplitChoice m64 = split_choice((M + 63) / 64 * ((N + 63) / 64), KT, pe, cap,
+                                         conv_cost(64, es, kr, dgrad, 64));
+    if (m64.us < best.us) best = ConvTiles{64, m64.s, m64.us, 64};
+  }
+  return best;
 }
-// split count of a convolution launch (the planner sizes partial sums with it)
-inline int conv_split_count(long long M, int N, int KT, size_t cap, int es) {
-  return conv_tiles(M, N, KT, cap, es).splits;
-}
-// Tile width of a convolution launch whose split count is fixed (the
-// forward launches of one layer all use the layer's count, so every output
-// element sums K in the same chunks whatever the band); `us` its estimate.
+// Tiles of a convolution launch whose split count is fixed (the forward
+// launches of one layer all use the layer's count, so every output element
+// sums K in the same chunks whatever the band); `us` its estimate.
 inline ConvTiles conv_tiles_split(long long M, int N, int KT, int s, int es,
-                                  int kr = LRCNN_CONV_KR) {
-  const double f = (es == 2 ? 0.75 : 1.0) * kr / 4.0;
-  const long long mt = (M + 127) / 128;
-  const double u64 = split_cost(mt * ((N + 63) / 64), KT, M * (long long)N,
-                                SplitCost{LRCNN_STEP_N64 * f, kr > 4 ? 2 : 3, 5.0}, s);
-  if (N <= 64 || kr > 4) return ConvTiles{64, s, u64};
-  const double u128 = split_cost(mt * ((N + 127) / 128), KT, M * (long long)N,
-                                 SplitCost{LRCNN_STEP_N128 * f, 2, 5.0}, s);
-  return u64 < u128 * LRCNN_NARROW_GAIN ? ConvTiles{64, s, u64} : ConvTiles{128, s, u128};
+                                  int kr = LRCNN_CONV_KR, bool small = false) {
+  const long long mt = (M + 127) / 128, pe = M * (long long)N;
+  const double u64 = split_cost(mt * ((N + 63) / 64), KT, pe, conv_cost(64, es, kr, false), s);
+  ConvTiles best{64, s, u64, 128};
+  if (N > 64 && kr <= 4) {
+    const double u128 = split_cost(mt * ((N + 127) / 128), KT, pe, conv_cost(128, es, kr, false), s);
+    if (!(u64 < u128 * LRCNN_NARROW_GAIN)) best = ConvTiles{128, s, u128, 128};
+  }
+  if (small) {
+    const double m64 = split_cost((M + 63) / 64 * ((N + 63) / 64), KT, pe,
+                                  conv_cost(64, es, kr, false, 64), s);
+    if (m64 < best.us) best = ConvTiles{64, s, m64, 64};
+  }
+  return best;
 }
 // K iterations of a conv for storage element size es (bytes); one
 // iteration covers kr 16-byte vectors of a tile row (LRCNN_CONV_KR, or
@@ -315,6 +356,14 @@ inline int conv_k_iters(int kh, int kw, int kc, int n, int es, bool dgrad = fals
   if (conv_tap_packed(kc, es, dgrad)) return (kh * kw + LRCNN_CONV_KR - 1) / LRCNN_CONV_KR;
   const int bk = 16 * kr / es;
   return kh * kw * ((kc + bk - 1) / bk);
+}
+
+// Tiles and split count of an input-gradient launch (dense: stride 1, or a
+// phase of a strided kernel).
+inline ConvTiles conv_dgrad_tiles(long long M, int N, int kh, int kw, int kc, size_t cap, int es,
+                                  bool dense) {
+  return conv_tiles(M, N, conv_k_iters(kh, kw, kc, N, es, true), cap, es, LRCNN_CONV_KR, true,
+                    dense && conv_vec(kh, kw, kc, N, es, true));
 }
 
 struct WgradArgs {

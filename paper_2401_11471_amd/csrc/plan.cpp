@@ -335,8 +335,8 @@ static constexpr size_t kPartCap = (size_t)LRCNN_PART_MIB << 20;
 // K chunks in the same order whatever band computes it: the row-centric and
 // layer-wise forwards (and the ReLU / argmax decisions) are then bitwise
 // equal. The count is the one with the smallest summed duration estimate
-// over those launches (the layer-wise launch in row chunks whose partial
-// sums fit the buffer), among the counts whose partial sums fit the buffer
+// over the bands' launches (with a single band, and the layer-wise launch in
+// row chunks whose partial sums fit the buffer), among the counts whose partial sums fit the buffer
 // at every row-centric launch.
 static void forward_splits(Plan &P,
                            const std::vector<const std::vector<std::vector<Rows>> *> &tabs) {
@@ -352,6 +352,9 @@ static void forward_splits(Plan &P,
     const Shape &su = P.shp[d.in0], &sv = P.shp[v];
     const int kr = conv_kr(d.kh, d.kw, su.c, sv.c, P.es, false);
     const int KT = conv_k_iters(d.kh, d.kw, su.c, sv.c, P.es, false, kr);
+    // (float32 counts are those of 128-row tiles: fewer splits would sum K in
+    // another order)
+    const bool vec = P.es == 2 && conv_vec(d.kh, d.kw, su.c, sv.c, P.es, false);
     std::vector<long long> ms;
     long long mmax = 0;
     for (auto *tab : tabs)
@@ -366,14 +369,22 @@ static void forward_splits(Plan &P,
       if (!split_valid(KT, sp)) continue;
       if (sp > 1 && (size_t)sp * (size_t)mmax * sv.c * 4 > kPartCap) break;
       double t = 0;
-      for (long long m : ms) t += conv_tiles_split(m, sv.c, KT, sp, P.es, kr).us;
-      // the layer-wise launch, in chunks of rows
+      for (long long m : ms) t += conv_tiles_split(m, sv.c, KT, sp, P.es, kr, vec).us;
+      // the layer-wise launch, in chunks of rows (a bfloat16 plan of several bands is
+      // made to run them, so the layer-wise baseline does not decide)
+      if (P.es == 2 && ms.size() > 2) {
+        if (best < 0 || t < best * 0.98) {
+          best = t;
+          best_s = sp;
+        }
+        continue;
+      }
       const size_t row_part = (size_t)sp * B * sv.w * sv.c * 4;
       const int rows = sp > 1 ? (int)std::min<size_t>(sv.h, std::max<size_t>(1, kPartCap / row_part))
                               : sv.h;
       const int full = sv.h / rows, rest = sv.h - full * rows;
-      t += full * conv_tiles_split(B * rows * sv.w, sv.c, KT, sp, P.es, kr).us;
-      if (rest) t += conv_tiles_split(B * rest * sv.w, sv.c, KT, sp, P.es, kr).us;
+      t += full * conv_tiles_split(B * rows * sv.w, sv.c, KT, sp, P.es, kr, vec).us;
+      if (rest) t += conv_tiles_split(B * rest * sv.w, sv.c, KT, sp, P.es, kr, vec).us;
       if (best < 0 || t < best * 0.98) {
         best = t;
         best_s = sp;
@@ -485,8 +496,8 @@ static void layout(Plan &P, Layout &L, const Fuse &F, const std::vector<int> &ca
         const int ext = bwd_covers(u0, u1, qu.lo, qu.hi) ? qu.hi - qu.lo : u1 - u0;
         for (int rows_ = ext;; rows_ = u1 - u0) {
           const long long md = (long long)P.cfg.batch * rows_ * su.w;
-          const int sd =
-              conv_split_count(md, su.c, conv_k_iters(d.kh, d.kw, sv.c, su.c, P.es, true), pcap, P.es);
+          const int sd = conv_dgrad_tiles(md, su.c, d.kh, d.kw, sv.c, pcap, P.es,
+                                          d.sh == 1 && d.sw == 1).splits;
           if (sd > 1) part = std::max(part, (size_t)(sd * md * su.c * 4));
           if (rows_ == u1 - u0 || P.cons[d.in0].size() == 1) break;
         }
