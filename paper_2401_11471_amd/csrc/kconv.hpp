@@ -64,14 +64,40 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
   // addresses derived from it, in scalar registers)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int R = a.y1 - a.y0;
-  const int M = a.B * R * a.Wd;
+  // output-channel tiles fastest: a run of consecutive pixel tiles per XCD
+  TileId tl = xcd_tile(true);
+  int py0 = a.y0, py1 = a.y1, px0 = a.px0, Wd = a.Wd, kh = a.kh, kw = a.kw, ty0 = a.ty0,
+      tx0 = a.tx0;
+  FastDiv ffw = a.fw, ffr = a.fr;
+  if (DGRAD && S1 && VEC && a.merged) {
+    // one of the four phases of a stride-2 input gradient (neighbouring
+    // tiles: they read the same error rows, and every XCD gets all of them)
+    const int ry = (tl.y >> 1) & 1, rx = tl.y & 1;
+    tl.y >>= 2;
+    const auto &py = ry ? a.phy[1] : a.phy[0];
+    const auto &px = rx ? a.phx[1] : a.phx[0];
+    py0 = py.first;
+    py1 = py0 + py.count;
+    kh = py.taps;
+    ffr = py.f;
+    px0 = px.first;
+    Wd = px.count;
+    kw = px.taps;
+    ffw = px.f;
+    ty0 = ry;
+    tx0 = rx;
+    const bool none = kh * kw == 0;
+    if (none) kh = 0, kw = 1;
+    // a phase without pixels here, or without taps where nothing needs
+    // initializing
+    if (tl.x * BM >= a.B * (py1 - py0) * Wd || (none && !a.dst_init)) return;
+  }
+  const int R = py1 - py0;
+  const int M = a.B * R * Wd;
   // pixel stride of a phase of a strided input gradient (else 1)
   const int ps = DGRAD && a.pst > 1 ? a.pst : 1;
-  // output-channel tiles fastest: a run of consecutive pixel tiles per XCD
-  const TileId tl = xcd_tile(true);
   const int m0 = tl.x * BM, n0 = tl.y * BN;
-  const int taps = a.kh * a.kw;
+  const int taps = kh * kw;
   const int CB = (a.KC + BK - 1) / BK;
   const bool tpk = !VEC && !DGRAD && a.tpack;
   const int KT = tpk ? (taps + KR - 1) / KR : taps * CB;
@@ -97,10 +123,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
     am[i] = m < M;
     int mm = am[i] ? m : 0;
     uint32_t t, x, b, y;
-    fdiv_qr((uint32_t)mm, a.fw, t, x);
-    fdiv_qr(t, a.fr, b, y);
-    ax[i] = a.px0 + ps * (int)x;
-    ay[i] = a.y0 + ps * (int)y;
+    fdiv_qr((uint32_t)mm, ffw, t, x);
+    fdiv_qr(t, ffr, b, y);
+    ax[i] = px0 + ps * (int)x;
+    ay[i] = py0 + ps * (int)y;
     abase[i] = (long long)b * a.src.bs - (long long)a.src.row0 * srow;
   }
   // source row / column of each A row before the tap offset, and its
@@ -140,7 +166,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
   if (MASK) {
 #pragma unroll
     for (int i = 0; i < NA; ++i)
-      tmask[i] = am[i] ? tap_window_mask(by[i], bx[i], a.kh, a.kw, a.sy0, a.sy1, a.Ws, DGRAD)
+      tmask[i] = am[i] ? tap_window_mask(by[i], bx[i], kh, kw, a.sy0, a.sy1, a.Ws, DGRAD)
                        : 0ull;
   }
   // B operand. Forward: B[k][n] = W[n][tap][k], contiguous along k, stored
@@ -180,7 +206,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
   const int kbeg = tl.z * a.kts;
   const int kend = min(KT, kbeg + a.kts);
   int tap = kbeg / CB, cbi = kbeg - (kbeg / CB) * CB;
-  int ti = tap / a.kw, tj = tap - (tap / a.kw) * a.kw;
+  int ti = tap / kw, tj = tap - (tap / kw) * kw;
   int kpk = kbeg;  // tap-packed forward: current K iteration
   // tap-mask loaders: byte offsets of the current (tap, channel block) in
   // the source (+-(ti * row pitch + tj * C) + cb) and in the weights
@@ -193,12 +219,12 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
   long long ub = (SG * ((long long)ti * srow + (long long)tj * a.src.C) + cbi * BK) * ES;
   const long long d_step = BK * ES, d_tap = (SG * a.src.C - (long long)(CB - 1) * BK) * ES;
   const long long d_row =
-      (SG * (srow - (long long)(a.kw - 1) * a.src.C) - (long long)(CB - 1) * BK) * ES;
+      (SG * (srow - (long long)(kw - 1) * a.src.C) - (long long)(CB - 1) * BK) * ES;
   const long long wst = DGRAD ? (long long)wtaps * a.N : 1;  // per channel
   const long long wtp = DGRAD ? a.N : a.KC;                 // per tap
   const int dwt = ps > 1 ? ps : 1;                          // next tap in a row
-  const int dwr = ps > 1 ? ps * a.kw_full - ps * (a.kw - 1) : 1;  // next kernel row
-  const int wtap0 = ps > 1 ? (a.ty0 + ps * ti) * a.kw_full + a.tx0 + ps * tj : tap;
+  const int dwr = ps > 1 ? ps * a.kw_full - ps * (kw - 1) : 1;  // next kernel row
+  const int wtap0 = ps > 1 ? (ty0 + ps * ti) * a.kw_full + tx0 + ps * tj : tap;
   long long wb = ((long long)cbi * BK * wst + (long long)wtap0 * wtp) * ES;
   const long long dw_step = BK * wst * ES;
   const long long dw_tap = (-(long long)(CB - 1) * BK * wst + (long long)dwt * wtp) * ES;
@@ -230,9 +256,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
       const int m = m0 + tid / PCR + RPR * i;
       const bool ok = m < M && pn < a.N;
       uint32_t t_, x_, b_, y_;
-      fdiv_qr((uint32_t)(ok ? m : 0), a.fw, t_, x_);
-      fdiv_qr(t_, a.fr, b_, y_);
-      const int x = a.px0 + (int)x_, y = a.y0 + (int)y_, b = (int)b_;
+      fdiv_qr((uint32_t)(ok ? m : 0), ffw, t_, x_);
+      fdiv_qr(t_, ffr, b_, y_);
+      const int x = px0 + (int)x_, y = py0 + (int)y_, b = (int)b_;
       const long long ro = b * a.res.bs + (y - a.res.row0) * drw + (long long)x * a.N + pn;
       pre_res[i] = load16z(a.res.p, ro * (long long)sizeof(T), ok);
     }
@@ -352,7 +378,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
       if (DGRAD) {
         const int o = cb + bk0 + BKS * j;
         ok = bvld[j] & (o < a.KC);
-        const int wtap = ps > 1 ? (a.ty0 + ps * ti) * a.kw_full + a.tx0 + ps * tj : tap;
+        const int wtap = ps > 1 ? (ty0 + ps * ti) * a.kw_full + tx0 + ps * tj : tap;
         off = bbase[j] + ((long long)cb * wtaps + wtap) * a.N;
         blim = a.N - bn[j];
       } else {
@@ -373,7 +399,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
     cbi = wrap ? 0 : cbi;
     tap += wrap ? 1 : 0;
     tj += wrap ? 1 : 0;
-    const bool nrow = tj == a.kw;
+    const bool nrow = tj == kw;
     tj = nrow ? 0 : tj;
     ti += nrow ? 1 : 0;
     if (MASK) {
@@ -596,9 +622,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
       const int m = m0 + r;
       if (m >= M || n >= a.N) continue;
       uint32_t t_, x_, b_, y_;
-      fdiv_qr((uint32_t)m, a.fw, t_, x_);
-      fdiv_qr(t_, a.fr, b_, y_);
-      const int x = a.px0 + ps * (int)x_, y = a.y0 + ps * (int)y_, b = (int)b_;
+      fdiv_qr((uint32_t)m, ffw, t_, x_);
+      fdiv_qr(t_, ffr, b_, y_);
+      const int x = px0 + ps * (int)x_, y = py0 + ps * (int)y_, b = (int)b_;
       const long long off = b * a.dst.bs + (y - a.dst.row0) * drow + (long long)x * a.N + n;
       uint4 q = *(const uint4 *)&Ct[(r - h0) * CP + cc * E];
       if (a.res.p) {
@@ -632,7 +658,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
         uint64_t bits = 0;
 #pragma unroll
         for (int e = 0; e < E; ++e) bits |= (uint64_t)(ldf(&w.e[e]) > 0.f ? 1 : 0) << (8 * e);
-        uint8_t *mk = a.mask + (((long long)b * a.mask_h + y) * a.Wd + x) * a.N + n;
+        uint8_t *mk = a.mask + (((long long)b * a.mask_h + y) * Wd + x) * a.N + n;
         if (mask_vec) {
           if (E == 8) *(uint64_t *)mk = bits;
           else *(uint32_t *)mk = (uint32_t)bits;
@@ -671,9 +697,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
       const int m = m0 + r;
       if (m >= M || n >= a.N) continue;
       uint32_t t_, x_, b_, y_;
-      fdiv_qr((uint32_t)m, a.fw, t_, x_);
-      fdiv_qr(t_, a.fr, b_, y_);
-      const int x = a.px0 + ps * (int)x_, y = a.y0 + ps * (int)y_, b = (int)b_;
+      fdiv_qr((uint32_t)m, ffw, t_, x_);
+      fdiv_qr(t_, ffr, b_, y_);
+      const int x = px0 + ps * (int)x_, y = py0 + ps * (int)y_, b = (int)b_;
       float4 *d = (float4 *)((float *)a.dst.p + b * a.dst.bs + (y - a.dst.row0) * drow +
                              (long long)x * a.N + n);
       const float4 q = *(const float4 *)&Ct[(r - h0) * FP + cc * 4];
@@ -692,9 +718,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
       const int m = m0 + wm + 32 * i + acc_row(v, lane);
       if (m >= M) continue;
       uint32_t t_, x_, b_, y_;
-      fdiv_qr((uint32_t)m, a.fw, t_, x_);
-      fdiv_qr(t_, a.fr, b_, y_);
-      const int x = a.px0 + ps * (int)x_, y = a.y0 + ps * (int)y_, b = (int)b_;
+      fdiv_qr((uint32_t)m, ffw, t_, x_);
+      fdiv_qr(t_, ffr, b_, y_);
+      const int x = px0 + ps * (int)x_, y = py0 + ps * (int)y_, b = (int)b_;
       const long long off = b * a.dst.bs + (y - a.dst.row0) * drow + (long long)x * a.N;
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
@@ -711,7 +737,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
           if (a.relu) val = val > 0.f ? val : 0.f;
           stf((T *)a.dst.p + off + n, val);
           if (a.mask)
-            a.mask[(((long long)b * a.mask_h + y) * a.Wd + x) * a.N + n] =
+            a.mask[(((long long)b * a.mask_h + y) * Wd + x) * a.N + n] =
                 val > 0.f ? 1 : 0;
         }
       }
@@ -1257,6 +1283,58 @@ static int conv_dispatch(const ConvArgs &a, hipStream_t s) {
       ph += 5.0 + conv_dgrad_tiles((long long)a.B * py.count * px.count, a.N, py.taps, px.taps,
                                    a.KC, cap, es, true).us;
     }
+  if (a.sh == 2 && conv_vec(a.kh, a.kw, a.KC, a.N, es, true) && a.B > 0) {
+    // the four phases of a stride of 2 in one launch, unless splitting their
+    // K loops (few tiles) makes separate ones cheaper
+    ConvArgs b = a;
+    long long mmax = 0, it128 = 0, it64 = 0;
+    int kt = 0;
+    double fl = 0;
+    const int nt = (a.N + 63) / 64;
+    for (int r = 0; r < 2; ++r) {
+      const PhaseDim py = phase_dim(a.y0, a.y1, a.ph, a.kh, 2, r);
+      const PhaseDim px = phase_dim(0, a.Wd, a.pw, a.kw, 2, r);
+      b.phy[r] = {py.first, py.count, py.taps, fast_div((uint32_t)std::max(1, py.count))};
+      b.phx[r] = {px.first, px.count, px.taps, fast_div((uint32_t)std::max(1, px.count))};
+    }
+    for (int p = 0; p < 4; ++p) {
+      const auto &py = b.phy[p >> 1], &px = b.phx[p & 1];
+      const long long m = (long long)a.B * py.count * px.count;
+      const int k = py.taps * px.taps == 0
+                        ? 0 : conv_k_iters(py.taps, px.taps, a.KC, a.N, es, true);
+      mmax = std::max(mmax, m);
+      kt = std::max(kt, k);
+      it128 += (m + 127) / 128 * nt * k;
+      it64 += (m + 63) / 64 * nt * k;
+      fl += 2.0 * m * py.taps * px.taps * a.KC * a.N;
+    }
+    auto est = [&](long long it, int bm) {
+      const SplitCost c = conv_cost(64, es, LRCNN_CONV_KR, true, bm);
+      return std::max(kt * std::max(c.lat_us, c.step_us),
+                      (double)it / 256.0 * c.step_us * c.share) + c.fixed_us;
+    };
+    const double m128 = est(it128, 128), m64 = est(it64, 64);
+    if (std::min(m128, m64) < ph && (std::min(m128, m64) < one || g_phases == 1)) {
+      const int bm = m64 < m128 ? 64 : 128;
+      b.merged = 1;
+      b.pst = 2;
+      b.kw_full = a.kw;
+      b.taps_full = a.kh * a.kw;
+      b.kts = kt;
+      dim3 grid((unsigned)((mmax + bm - 1) / bm), 4 * nt, 1);
+      int pr = -1;
+      if (prof::on)
+        pr = prof::begin(std::string("conv_gemm_kernel<") + (sizeof(T) == 4 ? "float" : "bf16") +
+                             ", 64, dgrad, vec>", fl, s,
+                         conv_bytes<T, DGRAD>(a, M, 1, false), es);
+      if (bm == 64)
+        launch_timed(conv_gemm_kernel<T, 64, LRCNN_CONV_KR, DGRAD, true, true, false, 64>, grid, s,
+                     pr, b);
+      else
+        launch_timed(conv_gemm_kernel<T, 64, LRCNN_CONV_KR, DGRAD, true, true>, grid, s, pr, b);
+      return (int)hipGetLastError();
+    }
+  }
   if (ph >= one && g_phases != 1) return conv_launch<T, DGRAD>(a, s);
   for (int ry = 0; ry < a.sh; ++ry)
     for (int rx = 0; rx < a.sw; ++rx) {

@@ -129,6 +129,16 @@ struct ConvArgs {
   // of the kh_full x kw_full kernel; W is read with the full kernel's
   // strides (taps_full taps, kw_full columns)
   int pst, px0, ty0, tx0, kw_full, taps_full;
+  // all four phases of a stride-2 kernel in one launch (merged = 1, set by
+  // the launcher): grid.y runs over (output tile, phase), phase = 2 * (row
+  // phase) + column phase; the fields above and y0, y1, Wd, kh, kw, fw, fr
+  // are then taken per phase from these (first pixel, count, taps, division
+  // by the count)
+  int merged;
+  struct PhaseAxis {
+    int first, count, taps;
+    FastDiv f;
+  } phy[2], phx[2];
   // input gradient: where the producer's completed error goes
   ErrOut eo;
 };
