@@ -877,8 +877,13 @@ static double conv_bytes(const ConvArgs &a, long long M, int splits, bool epi) {
 // masked off (they may be NaN). Where a 32-pixel block of a wave has a
 // window that leaves the image, or whose dwords could leave the tensor, its
 // vectors are gathered element by element.
-// Wave tile: 32 MI pixels x 64 outputs. Bound by HBM (the output map) and
-// the shifting's VALU. One tap per vector with the operand staged through
+// Where rows and strides keep the parity of every window's first element
+// (ALN: W * C and the horizontal stride times C even), the packing starts at
+// the aligned element, one before the row's first if that is odd (lead, a
+// zero weight), so a vector is one aligned 16-byte fetch without a shift.
+// Wave tile: 32 MI pixels x 64 outputs. Bound by the address unit (a wave's
+// fetch touches its pixels' bytes several times) and HBM (the output map).
+// One tap per vector with the operand staged through
 // LDS took 119 us for 38 rows of the ResNet-50 stem at 8 x 2400 x 3600; the
 // stem's training step there went 14.9 -> 10.4 ms, a 224-pixel forward of
 // ResNet-50 at batch 16 2.77 -> 2.71 ms, the static forward of stem and first
@@ -887,6 +892,8 @@ struct RawVec {
   uint32_t d[5];
   int sh;
 };
+// (ALN: p is 4-byte aligned and the vector starts there)
+template <bool ALN>
 __device__ __forceinline__ RawVec first_dwords(const bf16 *p) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
   typedef __attribute__((address_space(1))) const u32x4 g_u32x4;
@@ -895,8 +902,12 @@ __device__ __forceinline__ RawVec first_dwords(const bf16 *p) {
   const u32x4 q = *(g_u32x4 *)at;
   RawVec r;
   r.d[0] = q.x, r.d[1] = q.y, r.d[2] = q.z, r.d[3] = q.w;
-  r.d[4] = *(g_u32 *)(at + 16);
-  r.sh = ((uintptr_t)p & 2) ? 16 : 0;
+  r.d[4] = 0;
+  r.sh = 0;
+  if (!ALN) {
+    r.d[4] = *(g_u32 *)(at + 16);
+    r.sh = ((uintptr_t)p & 2) ? 16 : 0;
+  }
   return r;
 }
 // elements [lo, hi) of the vector at p, zeros elsewhere, already in place
@@ -913,7 +924,11 @@ __device__ __forceinline__ RawVec first_elems(const bf16 *p, int lo, int hi) {
   r.sh = 0;
   return r;
 }
-template <int MI>
+// elements before a kernel row's first in its packing
+__device__ __host__ static inline int first_lead(bool aln, int pw, int kc) {
+  return aln ? (pw * kc) & 1 : 0;
+}
+template <int MI, bool ALN>
 __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tiles, int KP) {
   // KP: K padded to whole 16-element slices; weight rows have a pitch of an
   // odd number of 16-byte vectors (16 rows of a read on distinct banks)
@@ -923,6 +938,7 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 31, g = lane >> 5;
   const int RV = (int)a.fkw.d, rlen = a.kw * a.KC, nvec = a.kh * RV, KV = KP / 8;
+  const int lead = first_lead(ALN, a.pw, a.KC);
   const int WP = KP + 8;
   bf16 *Ws = (bf16 *)smem;
   bf16 *St = (bf16 *)(smem + 64 * WP * 2) + wave * 32 * SP;
@@ -935,18 +951,20 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
     uint32_t ti, v;
     fdiv_qr((uint32_t)q, a.fkw, ti, v);
     const bool ok = (n0 + n < a.N) & (q < nvec);
-    const bf16 *p = w + (long long)(n0 + n) * a.kh * rlen + (long long)ti * rlen + 8 * v;
-    const RawVec e = first_elems(p, 0, ok ? rlen - 8 * (int)v : 0);
+    const int e0 = 8 * (int)v - lead;
+    const bf16 *p = w + (long long)(n0 + n) * a.kh * rlen + (long long)ti * rlen + e0;
+    const RawVec e = first_elems(p, -e0, ok ? rlen - e0 : 0);
     *(uint4 *)(Ws + n * WP + 8 * q) = make_uint4(e.d[0], e.d[1], e.d[2], e.d[3]);
   }
   __syncthreads();
   // elements of a kernel row's last vector, as masks of its dwords
-  const int nl = rlen - 8 * (RV - 1);
+  const int nl = rlen + lead - 8 * (RV - 1);
   uint32_t lm[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) lm[k] = 2 * k + 1 < nl ? ~0u : 2 * k < nl ? 0xffffu : 0u;
+  const uint32_t fm = lead ? 0xffff0000u : ~0u;  // first dword of a row's first vector
   // pixels past a window that the last vector's dwords reach
-  const int over = (RV * 8 + 2 - rlen + a.KC - 1) / a.KC;
+  const int over = (RV * 8 + (ALN ? -lead : 2) - rlen + a.KC - 1) / a.KC;
   float csc[2], csh[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -988,12 +1006,12 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
     while (v >= RV) v -= RV, ++ti;
     auto fetch = [&](RawVec (&raw)[MI]) {
       const bool vok = ti < a.kh;
-      const int tr = vok ? ti : 0, e0 = 8 * v;
+      const int tr = vok ? ti : 0, e0 = 8 * v - lead;
       const long long ro = (long long)tr * srow + e0;
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
         if (in[i]) {
-          raw[i] = first_dwords(rp[i] + ro);
+          raw[i] = first_dwords<ALN>(rp[i] + ro);
         } else {
           const int sy = by[i] + tr;
           const bool ok = vok & am[i] & (sy >= a.sy0) & (sy < a.sy1);
@@ -1008,6 +1026,7 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
       const bool last = v == RV - 1, none = ti >= a.kh;
 #pragma unroll
       for (int k = 0; k < 4; ++k) mk[k] = none ? 0u : last ? lm[k] : ~0u;
+      if (ALN) mk[0] &= v == 0 ? fm : ~0u;
       v += 2;
       while (v >= RV) v -= RV, ++ti;
     };
@@ -1033,7 +1052,9 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
         } q;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          q.u[k] = __builtin_amdgcn_alignbit(cur[i].d[k + 1], cur[i].d[k], cur[i].sh) & mc[k];
+          q.u[k] = (ALN ? cur[i].d[k]
+                        : __builtin_amdgcn_alignbit(cur[i].d[k + 1], cur[i].d[k], cur[i].sh)) &
+                   mc[k];
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q.v, bq[j], acc[i][j], 0, 0, 0);
@@ -1125,8 +1146,12 @@ static int conv_first_launch(ConvArgs a, int M, hipStream_t s) {
     else
       hipLaunchKernelGGL(kernel, dim3(gx, ny), dim3(256), lds, s, a, tiles, KP);
   };
-  if (wide) go(conv_first_kernel<2>);
-  else go(conv_first_kernel<1>);
+  // (by the layer's sizes alone: all its launches pack K alike)
+  const bool aln = a.src.W * a.src.C % 2 == 0 && a.sw * a.KC % 2 == 0 && a.src.C == a.KC &&
+                   a.kw * a.KC + first_lead(true, a.pw, a.KC) <=
+                       8 * conv_row_vecs(a.kw, a.KC, 2);
+  if (wide) aln ? go(conv_first_kernel<2, true>) : go(conv_first_kernel<2, false>);
+  else aln ? go(conv_first_kernel<1, true>) : go(conv_first_kernel<1, false>);
   return (int)hipGetLastError();
 }
 
