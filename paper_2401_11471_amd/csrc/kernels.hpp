@@ -401,7 +401,8 @@ inline int wgrad_k_iters(long long K, int es) { return (int)((K + 64 / es - 1) /
 // for layers with at most 64 output channels; otherwise, in bfloat16, the
 // cheaper estimate of 64- and 128-row tiles (narrow tiles give more
 // workgroups when a layer has few output tiles; measured faster on the
-// ResNet-50 bands), and in float32 128 rows (measured faster on VGG-16).
+// ResNet-50 bands), and in float32 128 rows unless those fill the CUs
+// unevenly.
 #ifndef LRCNN_WG_NARROW
 #define LRCNN_WG_NARROW 1
 #endif
@@ -426,7 +427,12 @@ inline WgradTiles wgrad_tiles(int Co, long long N, long long K, size_t cap, int 
   if (Co <= 64) return WgradTiles{64, r64.s};
   const SplitChoice r128 = split_choice(((Co + 127) / 128) * nt, KT, (long long)Co * N, cap,
                                         SplitCost{f, 3, 12.0, LRCNN_WG_MAXS, LRCNN_WG_SHARE});
-  if (LRCNN_WG_NARROW && es == 2 && r64.us < r128.us) return WgradTiles{64, r64.s};
+  // float32: 64 rows where the 128-row grid leaves over a quarter of its last
+  // round of CUs idle (alone, 512 x 4608 over 6272 pixels: 288 workgroups 448
+  // us, 64 rows 369; 256 x 2304 over 34200, 252 workgroups: 399 and 403)
+  const long long g128 = ((Co + 127) / 128) * nt * r128.s;
+  const bool even = 4 * g128 >= 3 * 256 * ((g128 + 255) / 256);
+  if (LRCNN_WG_NARROW && (es == 2 || !even) && r64.us < r128.us) return WgradTiles{64, r64.s};
   return WgradTiles{128, r128.s};
 }
 inline int wgrad_split_count(int Co, long long N, long long K, size_t cap, int es) {
