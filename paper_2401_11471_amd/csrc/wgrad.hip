@@ -19,17 +19,17 @@ namespace lrcnn {
 #ifndef LRCNN_WG_KR
 #define LRCNN_WG_KR 4
 #endif
-// Epilogue of a weight-gradient tile: the wave's 64 x 32 NB accumulators
-// (rows m0 + [0, 64), columns n0 + [0, 32 NB)) go to dW (one split: dW =
+// Epilogue of a weight-gradient tile: the wave's 32 MB x 32 NB accumulators
+// (rows m0 + [0, 32 MB), columns n0 + [0, 32 NB)) go to dW (one split: dW =
 // or += the sum) or to the split's partial-sum slice.
-template <int NB>
+template <int MB, int NB>
 __device__ __forceinline__ void wgrad_store(const WgradArgs &a, float *dw,
-                                            const f32x16 (&acc)[2][NB], int m0, int n0,
+                                            const f32x16 (&acc)[MB][NB], int m0, int n0,
                                             int N, int z, int lane) {
   const int col = lane & 31;
   float *out = gridDim.z == 1 ? dw : a.out + (long long)z * a.Co * N;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int m = m0 + 32 * i + acc_row(v, lane);
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(256, LRCNN_WG_OCC) void wgrad_kernel(WgradArgs a, i
   }
   if (t < n) step(t, f0, f1);
 
-  wgrad_store<NB>(a, dw, acc, m0 + wm, n0 + wn, N, tl.z, lane);
+  wgrad_store<2, NB>(a, dw, acc, m0 + wm, n0 + wn, N, tl.z, lane);
 }
 
 // bfloat16 with channel counts that are multiples of 8: both operands are
@@ -333,17 +333,24 @@ __global__ __launch_bounds__(256, LRCNN_WG_OCC) void wgrad_kernel(WgradArgs a, i
 // place in the group, its channel vector, its tap) and tests its bounds
 // against scalar limits. Wave w's A copies fill tile rows 8w .. 8w+7 and
 // so do its B copies, so both operands of a tile row hold the same pixel.
-template <int WBM>
+// Tiles are WBM x 128, or WBM x 64 where all of taps * C_in fit in 64 columns
+// (a 1x1 layer of 64 input channels: half of a 128-wide tile would be zeros
+// fetched, staged and multiplied): ResNet-50's first block at 8 x 600 x 900, 32
+// bands, 15.61 -> 15.45 ms per step.
+template <int WBM, int BN>
 __global__ __launch_bounds__(256, LRCNN_WG_DMA_OCC) void wgrad_rowg_kernel(WgradArgs a,
                                                                            int kchunk,
                                                                            float *dw) {
   using T = bf16;
-  constexpr int E = 8, BK = 32, BN = 128, ST = LRCNN_WG_DMA_ST;
+  constexpr int E = 8, BK = 32, ST = LRCNN_WG_DMA_ST;
   static_assert(ST == 3 || ST == 4, "ring depth");
-  constexpr int FBN = WBM == 128 ? 128 : 64, NB = FBN / 64;
+  // waves: 2 x 2, or (64 x 128) 1 x 4 of 64 x 32
+  constexpr bool ROW4 = WBM == 64 && BN == 128;
+  constexpr int MB = ROW4 ? 2 : WBM / 64, FBN = ROW4 ? 64 : BN, NB = FBN / 64;
   constexpr int VA = WBM / E, RA = 64 / VA;  // vectors per A row, A rows per copy
   constexpr int NIA = 8 / RA;                // A copies per wave per tile
-  constexpr int NIB = 2;                     // B copies per wave per tile (4 rows each)
+  constexpr int VB = BN / E, RB = 64 / VB;   // the same for B
+  constexpr int NIB = 8 / RB;
   constexpr int LD = NIA + NIB;
   constexpr uint32_t ASB = BK * WBM * 2, BSB = BK * BN * 2;
   static_assert(4 * NIA * 1024 == ASB && 4 * NIB * 1024 == BSB, "copy cover");
@@ -377,7 +384,7 @@ __global__ __launch_bounds__(256, LRCNN_WG_DMA_OCC) void wgrad_rowg_kernel(Wgrad
   }
   // B: group place kbB[j], (tap, channel) vector nb; column offset of the
   // pixel under the tap relative to the group's first pixel
-  const int nb = n0 + E * ((lane % 16) ^ (KM<T, BN>::sw(lane / 16) << 2));
+  const int nb = n0 + E * ((lane % VB) ^ (KM<T, BN>::sw(lane / VB) << 2));
   const int tap = nb / a.Ci;
   const int bti = tap / a.kw, btj = tap - (tap / a.kw) * a.kw;
   const bool bnok = nb < N;
@@ -385,7 +392,7 @@ __global__ __launch_bounds__(256, LRCNN_WG_DMA_OCC) void wgrad_rowg_kernel(Wgrad
   uint32_t lB[NIB];
 #pragma unroll
   for (int j = 0; j < NIB; ++j) {
-    kbB[j] = 4 * j + lane / 16;
+    kbB[j] = RB * j + lane / VB;
     bx[j] = btj + kbB[j] * a.sw;
     lB[j] = (uint32_t)(((long long)bti * srow + (long long)bx[j] * a.src.C + (nb - tap * a.Ci)) *
                        ES);
@@ -463,17 +470,17 @@ __global__ __launch_bounds__(256, LRCNN_WG_DMA_OCC) void wgrad_rowg_kernel(Wgrad
   auto As = [&](int st) { return (const T *)(smem + st * ASB); };
   auto Bs = [&](int st) { return (const T *)(smem + ST * ASB + st * BSB); };
 
-  f32x16 acc[2][NB];
+  f32x16 acc[MB][NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  const int wm = WBM == 128 ? (wave & 1) * 64 : 0;
-  const int wn = WBM == 128 ? (wave >> 1) * 64 : wave * 32;
+  const int wm = ROW4 ? 0 : (wave & 1) * (WBM / 2);
+  const int wn = ROW4 ? wave * 32 : (wave >> 1) * (BN / 2);
   const int n = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
-  using FR = Frag<T, FBN, 4, 1, 1, WBM, BN>;
+  using FR = Frag<T, FBN, 4, 1, 1, WBM, BN, MB>;
   FR f0, f1;
   auto wait_tiles = [](int k) {
     if (ST > 3 && k >= 2) wait_vmcnt<(ST > 3 ? 2 : 0) * LD>();
@@ -518,7 +525,7 @@ __global__ __launch_bounds__(256, LRCNN_WG_DMA_OCC) void wgrad_rowg_kernel(Wgrad
     dstep(t + 1, f1, f0);
   }
   if (t < n) dstep(t, f0, f1);
-  wgrad_store<NB>(a, dw, acc, m0 + wm, n0 + wn, N, tl.z, lane);
+  wgrad_store<MB, NB>(a, dw, acc, m0 + wm, n0 + wn, N, tl.z, lane);
 }
 
 // dW += (first band: dW =) sum over the split partial sums in a fixed order
@@ -630,8 +637,15 @@ static int wgrad_dispatch(const WgradArgs &a0, float *dw, hipStream_t s) {
                          (avec && bvec ? ", vec>" : ", scalar>"),
                      2.0 * K * a.Co * N, s, wbytes, (int)sizeof(T));
   if (rowg) {
-    if (wbm == 64) launch_timed(wgrad_rowg_kernel<64>, grid, s, pr, a, kchunk_l, dw);
-    else launch_timed(wgrad_rowg_kernel<128>, grid, s, pr, a, kchunk_l, dw);
+    // (the same grid: one column tile either way)
+    const bool n64 = N <= 64;
+    if (wbm == 64) {
+      if (n64) launch_timed(wgrad_rowg_kernel<64, 64>, grid, s, pr, a, kchunk_l, dw);
+      else launch_timed(wgrad_rowg_kernel<64, 128>, grid, s, pr, a, kchunk_l, dw);
+    } else {
+      if (n64) launch_timed(wgrad_rowg_kernel<128, 64>, grid, s, pr, a, kchunk_l, dw);
+      else launch_timed(wgrad_rowg_kernel<128, 128>, grid, s, pr, a, kchunk_l, dw);
+    }
   } else if (wide) {
     if (wbm == 64) launch_timed(wgrad_kernel<T, 64, true, true, 8>, grid, s, pr, a, kchunk, dw);
     else launch_timed(wgrad_kernel<T, 128, true, true, 8>, grid, s, pr, a, kchunk, dw);
