@@ -56,6 +56,8 @@ def bench_name(mangled: str) -> str:
     if m:
         vec = m.group(2) == "true" and m.group(3) == "true"
         return f"wgrad_kernel<{m.group(1)}, {'vec' if vec else 'scalar'}>"
+    if n.startswith("conv_first_kernel"):
+        return "conv_first_kernel<bf16>"
     for short in ("conv_split_epilogue", "wgrad_reduce_kernel"):
         if n.startswith(short):
             return short
