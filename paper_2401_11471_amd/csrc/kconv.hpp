@@ -877,6 +877,8 @@ static double conv_bytes(const ConvArgs &a, long long M, int splits, bool epi) {
 // masked off (they may be NaN). Where a 32-pixel block of a wave has a
 // window that leaves the image, or whose dwords could leave the tensor, its
 // vectors are gathered element by element.
+// A residual add that the planner gives this layer (two branches of a
+// few-channel map and their sum) is computed in the 16-byte store loop.
 // Where rows and strides keep the parity of every window's first element
 // (ALN: W * C and the horizontal stride times C even), the packing starts at
 // the aligned element, one before the row's first if that is odd (lead, a
@@ -1085,12 +1087,29 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
       for (int k = 0; k < 4; ++k) {
         const int row = 8 * k + (lane >> 3), n = n0 + 8 * (lane & 7);
         const int m = m0 + 32 * i + row;
-        const uint4 q = *(const uint4 *)&St[row * SP + 8 * (lane & 7)];
+        uint4 q = *(const uint4 *)&St[row * SP + 8 * (lane & 7)];
         if (m < M && n < a.N) {
           uint32_t t_, x_, b_, y_;
           fdiv_qr((uint32_t)m, a.fw, t_, x_);
           fdiv_qr(t_, a.fr, b_, y_);
           const int y = a.y0 + (int)y_;
+          if (a.res.p) {
+            // fused residual add on the value as stored, then the add's ReLU
+            union {
+              uint4 u;
+              bf16 e[8];
+            } cv, rv;
+            cv.u = q;
+            rv.u = *(const uint4 *)((const bf16 *)a.res.p + (long long)b_ * a.res.bs +
+                                    (y - a.res.row0) * drow + (long long)x_ * a.N + n);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              float v = ldf(&cv.e[e]) + ldf(&rv.e[e]);
+              if (a.res_relu) v = v > 0.f ? v : 0.f;
+              stf(&cv.e[e], v);
+            }
+            q = cv.u;
+          }
           *(uint4 *)((bf16 *)a.dst.p + (long long)b_ * a.dst.bs + (y - a.dst.row0) * drow +
                      (long long)x_ * a.N + n) = q;
           if (a.mask) {
@@ -1121,7 +1140,7 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
 
 template <typename T>
 static int conv_first_launch(ConvArgs a, int M, hipStream_t s) {
-  if (a.res.p || a.splits > 1) return (int)hipErrorInvalidValue;
+  if (a.splits > 1) return (int)hipErrorInvalidValue;
   a.fw = fast_div((uint32_t)a.Wd);
   a.fr = fast_div((uint32_t)(a.y1 - a.y0));
   a.fkw = fast_div((uint32_t)conv_row_vecs(a.kw, a.KC, 2));
