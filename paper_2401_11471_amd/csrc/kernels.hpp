@@ -301,7 +301,11 @@ inline ConvTiles conv_tiles(long long M, int N, int KT, size_t cap, int es,
     if (!(n64.us < n128.us * LRCNN_NARROW_GAIN)) best = ConvTiles{128, n128.s, n128.us, 128};
   }
   if (small) {
-    const SplitChoice m64 = split_choice((M + 63) / 64 * ((N + 63) / 64), KT, pe, cap,
+    // (float32: with partial sums no larger than the large tiles', since they
+    // are part of every plan's workspace: a layer of 128 channels and a pooling
+    // at 16 x 44 x 33 in 7 overlapping bands would need 45.0 MB, not 40.6)
+    const size_t cap64 = es == 2 ? cap : best.splits > 1 ? (size_t)best.splits * (size_t)pe * 4 : 0;
+    const SplitChoice m64 = split_choice((M + 63) / 64 * ((N + 63) / 64), KT, pe, cap64,
                                          conv_cost(64, es, kr, dgrad, 64));
     if (m64.us < best.us) best = ConvTiles{64, m64.s, m64.us, 64};
   }

@@ -9,7 +9,7 @@
 import pytest
 
 from paper_2401_11471_amd import lrcnn as L
-from workloads import net_nodes, tiny_net, vgg16_net
+from workloads import NetBuilder, net_nodes, tiny_net, vgg16_net
 
 
 def a256(x):
@@ -111,3 +111,23 @@ def test_max_batch_row_centric_exceeds_layerwise_and_infeasible_budget():
     with pytest.raises(L.LrcnnError) as e:
         L.lrcnn_max_batch(nodes, 3, 600, 900, 1e6, L.BF16, L.CARRY, 8)
     assert e.value.code == -8
+
+
+@pytest.mark.parametrize("batch,side,bands", [(1, 160, 4), (1, 192, 8), (4, 80, 8)])
+def test_float32_vgg16_plans_fit_the_static_workspace(batch, side, bands):
+    # plans within a few MiB of the 64 MiB of lrcnn_forward_rows_static when
+    # a layer's weight-gradient partial sums (9.4 MB a split for 512 x 4608)
+    # are laid out beside the next layer's; they are needed from the layer's
+    # own backward step only
+    p = L.lrcnn_plan(vgg16_net(), batch, 3, side, side, L.F32, L.CARRY, bands)
+    assert p.info()["workspace_bytes"] <= L.STATIC_WORKSPACE_BYTES
+
+
+def test_small_tiles_need_no_larger_partial_sums():
+    # float32 input gradients: 40.6 MB with the partial sums of the large
+    # tiles' split, 45.0 with those that 64 x 64 tiles alone would choose
+    nb = NetBuilder()
+    v = nb.conv(0, 128, 3, 1, 1)
+    nb.pool(v, 2, 2)
+    p = L.lrcnn_plan(nb.nodes, 16, 128, 44, 33, L.F32, L.RECOMPUTE, 7)
+    assert p.info()["workspace_bytes"] <= 40_700_000
