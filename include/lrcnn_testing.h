@@ -39,9 +39,16 @@ void lrcnn_debug_fp_pipeline(int on);
 /* on != 0: on the calling thread, the backward launches every weight
  * gradient on the caller's stream, just before the input gradient it would
  * otherwise overlap, so that a profile times each kernel with the GPU to
- * itself; on == 0 (default) the weight gradients run on the plan's side
- * stream. Results are bitwise equal. */
+ * itself; on == 0 (default) those that lrcnn_debug_fork_wgrad tells run on
+ * the plan's side stream. Results are bitwise equal. */
 void lrcnn_debug_serial_wgrad(int on);
+
+/* On the calling thread, the weight gradients that the backward puts on the
+ * side stream: mode 0 = by estimate, all of them where the caller's stream is
+ * being captured in a graph (default), 1 = all, 2 = every other one. Returns
+ * how many the thread's calls put there since the last call of this function.
+ * Results are bitwise equal. */
+int lrcnn_debug_fork_wgrad(int mode);
 
 /* On the calling thread, the input gradient of a strided convolution
  * (stride s in both directions) is computed as s^2 launches, one per phase

@@ -25,6 +25,10 @@ thread_local bool g_dry = false;
 // cause is not yet known)
 thread_local bool g_no_fp_pipe = true;
 thread_local bool g_serial_wg = false;
+// weight gradients on the side stream: 0 = by Run::fork_wgrad, 1 = all, 2 =
+// every other one; and how many went there
+thread_local int g_fork_mode = 0;
+thread_local int g_forked = 0;
 
 #define LAUNCH(call, what)                                                 \
   do {                                                                     \
@@ -36,8 +40,8 @@ thread_local bool g_serial_wg = false;
 
 // The weight gradient of a convolution does not depend on the input
 // gradient of the same layer, and a band's launches of either are often too
-// small to fill the GPU, so the backward runs the longer weight gradients on
-// a side stream beside the caller's stream. Events order them: the side stream
+// small to fill the GPU, so the backward runs weight gradients (Run::fork_wgrad:
+// which) on a side stream beside the caller's stream. Events order them: the side stream
 // waits until the error operand is formed; the caller's stream waits for the
 // last weight gradient before the error-operand buffer is formed again and
 // at the end of every band (the next band's recompute overwrites the
@@ -61,6 +65,19 @@ bool ensure_side(Plan &P) {
   P.ev_wg = b;
   P.side_dev = dev;
   return true;
+}
+
+// Whether work enqueued on the stream is being captured in a graph. (The null
+// stream is not asked: it cannot be captured, and while another stream is,
+// asking for it is an error.)
+bool capturing(void *stream) {
+  if (!stream) return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing((hipStream_t)stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusActive;
 }
 
 // Events of the pipelined forward pass (created once per plan and device,
@@ -108,6 +125,8 @@ struct Run {
   std::vector<View> dinit_cv;
   std::vector<int> dinit_t;
   hipStream_t side = nullptr;  // weight-gradient stream (backward only)
+  bool fork_all = false;       // every weight gradient goes there (captured)
+  int n_wg = 0;                // weight gradients so far
   bool wg_pending = false;     // a weight gradient on `side` not yet joined
   bool dx_f32 = false;         // store dL/dx as float32 (a checkpoint's error)
   // forward pass pipelined over bands (two streams by band parity): band r's
@@ -606,6 +625,7 @@ struct Run {
         LAUNCH(launch_wgrad(dt, g, wdst, side), "weight gradient");
         LAUNCH(hipEventRecord((hipEvent_t)P.ev_wg, side), "event record");
         wg_pending = true;
+        ++g_forked;
       } else {
         LAUNCH(launch_wgrad(dt, g, wdst, stream), "weight gradient");
       }
@@ -741,17 +761,27 @@ struct Run {
     return LRCNN_OK;
   }
 
+  void use_side(const Plan &p) {
+    side = (hipStream_t)p.side_stream;
+    fork_all = capturing(stream);
+  }
+
   // Whether conv v's weight gradient over rows [a, b) goes to the side
-  // stream. A fork and its join cost the two queues about 10 us a conv, so it
-  // pays where an input gradient runs beside it (dgrad) and the weight
-  // gradient itself takes that long (estimated at 400 / 90 TFLOP/s and
-  // 4 TB/s). Per step, always forked -> by this rule, launched from the host:
-  // 224-pixel ResNet-50 16.4 -> 13.6 ms, block 2 at 28 x 28 layer-wise 160 ->
-  // 129 us, the tiny net 692 -> 545 us, ResNet-50's first block at 600 x 900
-  // 16.9 -> 15.7 ms, block 3 14.3 -> 13.1; as a replayed graph, where a join
-  // is cheaper, 224-pixel ResNet-50 13.1 -> 13.8 ms and 2400 x 3600 209 ->
-  // 212. From 40 us on the overlap of VGG-16 and block 4 is lost as well.
-  bool fork_wgrad(int v, int a, int b, bool dgrad) const {
+  // stream. Launched from the host, a fork and its join cost the two queues
+  // about 10 us a conv, so it pays where an input gradient runs beside it
+  // (dgrad) and the weight gradient itself takes that long (estimated at 400 /
+  // 90 TFLOP/s and 4 TB/s). Per step, always forked -> by this rule: 224-pixel
+  // ResNet-50 16.4 -> 13.6 ms, block 2 at 28 x 28 layer-wise 160 -> 133 us, the
+  // tiny net 692 -> 533 us, ResNet-50's first block at 600 x 900 16.9 -> 15.7
+  // ms, block 3 14.3 -> 13.1. From 40 us on the overlap of VGG-16 and block 4
+  // is lost as well. In a replayed graph a fork and join cost less, so all are
+  // forked where the stream is being captured (by the rule -> all): 224-pixel
+  // ResNet-50 12.18 -> 11.56 ms, 2400 x 3600 206.3 -> 203.8, VGG-16 at 224
+  // pixels 12.47 -> 12.49.
+  bool fork_wgrad(int v, int a, int b, bool dgrad) {
+    ++n_wg;
+    if (g_fork_mode) return g_fork_mode == 1 || n_wg % 2 == 0;
+    if (fork_all) return true;
     if (!dgrad) return false;
     const lrcnn_node &d = P.nodes[v];
     const Shape &sv = P.shp[v], &su = P.shp[d.in0];
@@ -983,7 +1013,7 @@ int hybrid_backward(Plan &P, const void *x, const void *const *w, const float *c
   Run run(C, C.lw, S_LAYERWISE, ws + P.h_col, ws + P.h_ck, w + c, sc ? sc + c : nullptr,
           sf ? sf + c : nullptr, stream);
   run.dx_f32 = true;
-  if (!g_dry && !g_serial_wg && ensure_side(C)) run.side = (hipStream_t)C.side_stream;
+  if (!g_dry && !g_serial_wg && ensure_side(C)) run.use_side(C);
   int st;
   if ((st = run.band_fwd(0, nullptr, nullptr, true, false, true)) != LRCNN_OK) return st;
   if ((st = run.begin_dw()) != LRCNN_OK) return st;
@@ -1078,7 +1108,7 @@ extern "C" int lrcnn_backward_rows(lrcnn_plan_t *plan, const void *x, const void
     return lrcnn_fail(LRCNN_ESTATE,
                       "CARRY backward needs a preceding lrcnn_forward_rows on this plan and workspace");
   Run run(P, P.rc, carry ? S_CARRY : S_RECOMPUTE, workspace, x, w, aff_scale, aff_shift, stream);
-  if (!g_dry && !g_serial_wg && ensure_side(P)) run.side = (hipStream_t)P.side_stream;
+  if (!g_dry && !g_serial_wg && ensure_side(P)) run.use_side(P);
   if ((st = run.begin_dw()) != LRCNN_OK) return st;
   float *dxacc = nullptr;
   if (!carry && dx) {
@@ -1124,7 +1154,7 @@ extern "C" int lrcnn_layerwise_reference_gpu(lrcnn_plan_t *plan, const void *x,
   if ((st = check_dw(P, dw)) != LRCNN_OK) return st;
   if ((st = check_ws(P.lw, workspace, ws_bytes)) != LRCNN_OK) return st;
   Run run(P, P.lw, S_LAYERWISE, workspace, x, w, aff_scale, aff_shift, stream);
-  if (!g_dry && !g_serial_wg && ensure_side(P)) run.side = (hipStream_t)P.side_stream;
+  if (!g_dry && !g_serial_wg && ensure_side(P)) run.use_side(P);
   // FP keeps every node's full map; BP reads them without recomputing.
   // The pool argmax is produced in FP (bp = true selects its buffer).
   if ((st = run.band_fwd(0, y, mask_out, true)) != LRCNN_OK) return st;
@@ -1149,6 +1179,12 @@ extern "C" void lrcnn_debug_dry_run(int on) { lrcnn::g_dry = on != 0; }
 extern "C" void lrcnn_debug_act_fusion(int on) { lrcnn::g_no_act_fusion = on == 0; }
 extern "C" void lrcnn_debug_fp_pipeline(int on) { lrcnn::g_no_fp_pipe = on == 0; }
 extern "C" void lrcnn_debug_serial_wgrad(int on) { lrcnn::g_serial_wg = on != 0; }
+extern "C" int lrcnn_debug_fork_wgrad(int mode) {
+  const int n = lrcnn::g_forked;
+  lrcnn::g_forked = 0;
+  lrcnn::g_fork_mode = mode;
+  return n;
+}
 extern "C" void lrcnn_debug_dgrad_phases(int mode) { lrcnn::set_dgrad_phases(mode); }
 
 extern "C" void lrcnn_debug_profile(int on) { lrcnn::profile_enable(on); }

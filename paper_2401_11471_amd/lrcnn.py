@@ -110,6 +110,8 @@ def _load():
     lib.lrcnn_debug_act_fusion.restype = None
     lib.lrcnn_debug_serial_wgrad.argtypes = [C.c_int]
     lib.lrcnn_debug_serial_wgrad.restype = None
+    lib.lrcnn_debug_fork_wgrad.argtypes = [C.c_int]
+    lib.lrcnn_debug_fork_wgrad.restype = C.c_int
     lib.lrcnn_debug_dgrad_phases.argtypes = [C.c_int]
     lib.lrcnn_debug_dgrad_phases.restype = None
     lib.lrcnn_debug_profile.argtypes = [C.c_int]
@@ -145,6 +147,7 @@ EXPORTS = ("lrcnn_plan", "lrcnn_plan_query", "lrcnn_plan_node_shape",
            "lrcnn_backward_rows", "lrcnn_layerwise_reference_gpu", "lrcnn_last_error",
            "lrcnn_debug_dry_run", "lrcnn_debug_fp_pipeline", "lrcnn_debug_act_fusion",
            "lrcnn_debug_dgrad_phases", "lrcnn_debug_serial_wgrad",
+           "lrcnn_debug_fork_wgrad",
            "lrcnn_debug_profile",
            "lrcnn_debug_profile_collect", "lrcnn_debug_profile_entry",
            "lrcnn_debug_profile_roofline",
@@ -332,9 +335,16 @@ def lrcnn_debug_fp_pipeline(on):
 
 
 def lrcnn_debug_serial_wgrad(on):
-    """Test hook: weight gradients on the caller's stream (on) or on the plan's
-    side stream beside the input gradients (off, the default)."""
+    """Test hook: all weight gradients on the caller's stream (on) or some on the
+    plan's side stream beside the input gradients (off, the default)."""
     LIB.lrcnn_debug_serial_wgrad(1 if on else 0)
+
+
+def lrcnn_debug_fork_wgrad(mode):
+    """Test hook: weight gradients on the side stream (0 by estimate, or all of
+    them in a captured graph; 1 all, 2 every other one). Returns how many went
+    there since the last call."""
+    return LIB.lrcnn_debug_fork_wgrad(int(mode))
 
 
 def lrcnn_debug_act_fusion(on):

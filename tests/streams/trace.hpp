@@ -17,3 +17,5 @@ struct TraceOp {
   std::vector<Span> spans;
 };
 extern std::vector<TraceOp> g_trace;
+// whether hipStreamIsCapturing reports a capture
+extern bool g_capturing;

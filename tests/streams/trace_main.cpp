@@ -12,7 +12,8 @@
 //    events leave unordered touch the same bytes with one of them writing
 //    (the stubs record each forward launch's rows of every buffer).
 // A case's final flag: bit 0 pipelines the forward over two streams, bit 1
-// checks the forward alone.
+// checks the forward alone, bit 2 makes hipStreamIsCapturing say that the
+// stream is captured.
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
@@ -81,13 +82,15 @@ static int check(const std::vector<TraceOp> &t, uintptr_t origin, int ncase) {
       ++bad;
     }
   // separate error-window initialisation launches (zeroing, carry copy-in)
-  int inits = 0;
+  int inits = 0, wg[2] = {0, 0};  // and weight gradients on / off the origin
+  for (const TraceOp &o : t)
+    if (o.kind == 'K' && !std::strcmp(o.what, "wgrad")) ++wg[o.stream != origin];
   for (const TraceOp &o : t)
     if (o.kind == 'K' && (!std::strcmp(o.what, "rows_init") || !std::strcmp(o.what, "rows_zero")))
       ++inits;
   std::printf("case %d: ops %zu streams %zu", ncase, t.size(), nops.size());
   for (auto &kv : nops) std::printf(" [%s %d]", kv.first == origin ? "origin" : "side", kv.second);
-  std::printf(" inits %d violations %d\n", inits, bad);
+  std::printf(" inits %d wgrad %d+%d violations %d\n", inits, wg[0], wg[1], bad);
   return bad;
 }
 
@@ -196,6 +199,7 @@ int main() {
     lrcnn_plan_info info{};
     lrcnn_plan_query(p, &info);
     lrcnn_debug_fp_pipeline(pipe & 1);
+    g_capturing = (pipe & 4) != 0;
     // placeholder device pointers, never dereferenced (the launchers are
     // stubs), each buffer in its own 2^40-byte range so that footprints of
     // distinct buffers never overlap

@@ -58,9 +58,12 @@ def test_graph_replay_matches_eager(net, dtype, mode, nb, refine):
     torch.cuda.current_stream().wait_stream(s)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
+    L.lrcnn_debug_fork_wgrad(0)
     with torch.cuda.graph(graph):
         step()
     torch.cuda.synchronize()
+    # a captured step puts every weight gradient on the side stream
+    assert L.lrcnn_debug_fork_wgrad(0) > nb * refine
 
     for rep in range(3):
         # eager work between replays: overwrite everything the step writes

@@ -229,18 +229,28 @@ def test_backward_without_forward_is_rejected():
 @pytest.mark.parametrize("dtype", [F32, BF16])
 def test_serial_weight_gradients_equal_overlapped(dtype):
     """Weight gradients on the caller's stream (the profiling schedule) give
-    the same bits as the default schedule on the side stream."""
+    the same bits as by the default rule, as all of them on the side stream,
+    and as every other one there (so that both kinds follow each other)."""
     nodes, inp = _inputs("resnet_like", dtype, seed=17)
-    base = gpu_run(nodes, inp, L.CARRY, 4, twin=False)
+    convs = sum(nd[0] == L.OP_CONV for nd in nodes)
     L.lrcnn_debug_serial_wgrad(True)
     try:
         ser = gpu_run(nodes, inp, L.CARRY, 4, twin=False)
     finally:
         L.lrcnn_debug_serial_wgrad(False)
-    np.testing.assert_array_equal(base["dx"], ser["dx"])
-    for v in range(1, len(nodes)):
-        if base["dw"][v] is not None:
-            np.testing.assert_array_equal(base["dw"][v], ser["dw"][v])
+    for mode in (0, 1, 2):
+        L.lrcnn_debug_fork_wgrad(mode)
+        try:
+            base = gpu_run(nodes, inp, L.CARRY, 4, twin=False)
+        finally:
+            forked = L.lrcnn_debug_fork_wgrad(0)
+        # (small layers: the rule forks none of them)
+        if mode:
+            assert forked >= 4 * convs // mode - 4, (mode, forked)
+        np.testing.assert_array_equal(base["dx"], ser["dx"])
+        for v in range(1, len(nodes)):
+            if base["dw"][v] is not None:
+                np.testing.assert_array_equal(base["dw"][v], ser["dw"][v])
 
 
 def test_profile_roofline_entries():

@@ -104,6 +104,25 @@ def test_block_outputs_need_no_separate_window_initialisation(checker):
     assert inits and max(inits) < 16 * c["bands"], r.stdout[-2000:]
 
 
+def test_captured_weight_gradients_all_fork(checker):
+    # launched from the host, weight gradients go to the side stream by
+    # estimate; where the caller's stream is being captured, all of them do
+    lines = []
+    for flag in (0, 4):
+        for cid in (1, 3, 5):
+            c = CONFIGS[cid]
+            lines.append(_line(net_nodes(c["net"]), c["batch"], c["h"], c["w"], c["dtype"],
+                               L.CARRY, c["bands"], pipe=flag))
+    r = _run(checker, lines)
+    assert r.returncode == 0, (r.stdout[-4000:], r.stderr[-4000:])
+    wg = [(int(a), int(b)) for a, b in re.findall(r"wgrad (\d+)\+(\d+)", r.stdout)]
+    assert len(wg) == 12  # two steps a case
+    host, captured = wg[:6], wg[6:]
+    assert host[0][1] == 0 and host[4][0] > 0 and host[4][1] > 0
+    for (a, b), (p, q) in zip(host, captured):
+        assert p == 0 and q == a + b
+
+
 def _planted(tmp_path, old, new, name):
     # the executor with a mistake planted on the CPU, built against the stubs
     src = (CSRC / "exec.cpp").read_text()
