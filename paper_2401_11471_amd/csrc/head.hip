@@ -29,7 +29,8 @@ constexpr int kMaxClasses = 64;
 // the finer chunks go into dy, which the last pass of the call overwrites:
 // K / 2048 x 64 classes x 4 bytes per image always fit its K x 2 bytes. With
 // K <= 2048 there is one chunk, and it goes to the workspace, which holds
-// the sums of chunks of kWsChunk features.
+// the sums of chunks of kWsChunk features; so do the sums of a call whose dy
+// shares memory with an input (dy written over y).
 constexpr int kChunk = 2048, kWsChunk = 8192;
 
 typedef uint16_t bf16;
@@ -92,11 +93,11 @@ __device__ __forceinline__ void stn(bf16 *p, const float (&v)[N]) {
 template <typename T, int V>
 __global__ __launch_bounds__(256) void head_partial_kernel(const T *y, const float *fw,
                                                            long long K, int C, int chunks,
-                                                           float *part) {
+                                                           int chunk, float *part) {
   __shared__ float red[kMaxClasses][4];
   const int ch = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const long long k0 = (long long)ch * kChunk;
-  const long long k1 = k0 + kChunk < K ? k0 + kChunk : K;
+  const long long k0 = (long long)ch * chunk;
+  const long long k1 = k0 + chunk < K ? k0 + chunk : K;
   float acc[kMaxClasses];
 #pragma unroll
   for (int c = 0; c < kMaxClasses; ++c) acc[c] = 0.f;
@@ -177,12 +178,13 @@ __global__ __launch_bounds__(256) void head_softmax_kernel(const float *part, in
 
 // dy[b, k] = sum_c dlog[b, c] * fc_w[c, k] (storage dtype) and
 // dfc_w[c, k] = sum_b dlog[b, c] * y[b, k], V features per thread, in one
-// launch (they do not depend on each other).
+// launch (they do not depend on each other). Vectors [from, to) of the two, so
+// that a call with a gradient written over an input runs dy before dfc_w.
 template <typename T, int V>
 __global__ void head_grad_kernel(const float *dlog, const float *fw, const T *y, long long K,
-                                 int B, int C, T *dy, float *dfw) {
-  const long long KV = K / V, ny = (long long)B * KV, total = ny + (long long)C * KV;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
+                                 int B, int C, T *dy, float *dfw, long long from, long long to) {
+  const long long KV = K / V, ny = (long long)B * KV;
+  for (long long i = from + (long long)blockIdx.x * blockDim.x + threadIdx.x; i < to;
        i += (long long)gridDim.x * blockDim.x) {
     const bool isy = i < ny;
     const long long j = isy ? i : i - ny;
@@ -292,7 +294,7 @@ unsigned blocks_for(long long n) {
 
 struct HeadLayout {
   long long K;
-  int B, chunks;
+  int B, chunks, ws_chunks;
   size_t part, dlog, lossv, total;
 };
 HeadLayout head_layout(const Plan &P, int C) {
@@ -301,16 +303,19 @@ HeadLayout head_layout(const Plan &P, int C) {
   h.K = (long long)s.h * s.w * s.c;
   h.B = P.cfg.batch;
   h.chunks = (int)((h.K + kChunk - 1) / kChunk);
-  const int ws_chunks = (int)((h.K + kWsChunk - 1) / kWsChunk);
+  h.ws_chunks = (int)((h.K + kWsChunk - 1) / kWsChunk);
   auto a256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
   h.part = 0;
-  h.dlog = a256((size_t)h.B * ws_chunks * C * 4);
+  h.dlog = a256((size_t)h.B * h.ws_chunks * C * 4);
   h.lossv = a256(h.dlog + (size_t)h.B * C * 4);
   h.total = a256(h.lossv + (size_t)h.B * 4);
   return h;
 }
 
 bool misaligned(const void *p) { return ((uintptr_t)p & 15u) != 0; }
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
 
 }  // namespace
 }  // namespace lrcnn
@@ -345,29 +350,48 @@ extern "C" int lrcnn_head_loss(const lrcnn_plan_t *plan, const void *y, const fl
                                             " bytes, got " + std::to_string(head_ws_bytes));
   hipStream_t s = (hipStream_t)stream;
   char *ws = (char *)head_ws;
-  float *part = h.chunks > 1 ? (float *)dy : (float *)(ws + h.part), *dlog = (float *)(ws + h.dlog),
-        *lossv = (float *)(ws + h.lossv);
+  float *dlog = (float *)(ws + h.dlog), *lossv = (float *)(ws + h.lossv);
   const int C = n_classes;
   const bool bf = P.cfg.dtype == LRCNN_BF16;
-  dim3 g1(h.chunks, h.B);
+  // gradients may be written over inputs: dy over y (d_fc_w then comes from
+  // what is left there), d_fc_w over fc_w
+  const size_t ny = (size_t)h.B * h.K * (bf ? 2 : 4), nw = (size_t)C * h.K * 4;
+  const bool dy_in = overlap(dy, ny, y, ny) || overlap(dy, ny, fc_w, nw) ||
+                     overlap(dy, ny, fc_b, (size_t)C * 4) || overlap(dy, ny, labels, (size_t)h.B * 4);
+  const bool in_place = dy_in || overlap(d_fc_w, nw, fc_w, nw) || overlap(d_fc_w, nw, y, ny);
+  const bool in_dy = h.chunks > 1 && !dy_in;
+  float *part = in_dy ? (float *)dy : (float *)(ws + h.part);
+  const int chunk = in_dy ? kChunk : kWsChunk, chunks = in_dy ? h.chunks : h.ws_chunks;
+  dim3 g1(chunks, h.B);
   // (4-wide accesses when every image's and class's row keeps them aligned)
   const bool v4 = h.K % 4 == 0;
   auto partial = [&](auto *yp) {
     using T = std::remove_const_t<std::remove_pointer_t<decltype(yp)>>;
-    if (v4) head_partial_kernel<T, 4><<<g1, 256, 0, s>>>(yp, fc_w, h.K, C, h.chunks, part);
-    else head_partial_kernel<T, 1><<<g1, 256, 0, s>>>(yp, fc_w, h.K, C, h.chunks, part);
+    if (v4) head_partial_kernel<T, 4><<<g1, 256, 0, s>>>(yp, fc_w, h.K, C, chunks, chunk, part);
+    else head_partial_kernel<T, 1><<<g1, 256, 0, s>>>(yp, fc_w, h.K, C, chunks, chunk, part);
   };
   auto grads = [&](auto *yp) {
     using T = std::remove_const_t<std::remove_pointer_t<decltype(yp)>>;
-    const unsigned g = blocks_for((long long)(h.B + C) * h.K / (v4 ? 4 : 1));
-    if (v4)
-      head_grad_kernel<T, 4><<<g, 256, 0, s>>>(dlog, fc_w, yp, h.K, h.B, C, (T *)dy, d_fc_w);
-    else
-      head_grad_kernel<T, 1><<<g, 256, 0, s>>>(dlog, fc_w, yp, h.K, h.B, C, (T *)dy, d_fc_w);
+    const long long kv = h.K / (v4 ? 4 : 1), mid = h.B * kv, end = mid + C * kv;
+    auto run = [&](long long from, long long to) {
+      const unsigned g = blocks_for(to - from);
+      if (v4)
+        head_grad_kernel<T, 4><<<g, 256, 0, s>>>(dlog, fc_w, yp, h.K, h.B, C, (T *)dy, d_fc_w,
+                                                 from, to);
+      else
+        head_grad_kernel<T, 1><<<g, 256, 0, s>>>(dlog, fc_w, yp, h.K, h.B, C, (T *)dy, d_fc_w,
+                                                 from, to);
+    };
+    if (in_place) {
+      run(0, mid);
+      run(mid, end);
+    } else {
+      run(0, end);
+    }
   };
   if (bf) partial((const bf16 *)y);
   else partial((const float *)y);
-  head_softmax_kernel<<<1, 256, 0, s>>>(part, h.chunks, fc_b, labels, h.B, C, logits, dlog,
+  head_softmax_kernel<<<1, 256, 0, s>>>(part, chunks, fc_b, labels, h.B, C, logits, dlog,
                                         lossv, loss, d_fc_b);
   if (bf) grads((const bf16 *)y);
   else grads((const float *)y);

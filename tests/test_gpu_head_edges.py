@@ -2,7 +2,8 @@
 features that fill one, two or four-wide accesses and end on, before or
 after a 2048-feature chunk, the fewest and most classes, more images and
 classes than one block has threads, and an update of more tensors than one
-launch takes, with weights shared by two layers (updated twice, in order)."""
+launch takes, with weights shared by two layers (updated twice, in order). And
+gradients written over the inputs they do not need any more."""
 import numpy as np
 import pytest
 import torch
@@ -58,6 +59,45 @@ def test_head_edges(batch, k, classes, dtype):
     if classes > 1:
         assert rel(dfw, rdfw) < 1e-5 and rel(dfb, rdfb) < 1e-5
         assert rel(dy, rdy) < (1e-5 if dtype == F32 else 2.0 ** -8)
+
+
+@pytest.mark.parametrize("over", ["dy_over_y", "d_fc_w_over_fc_w"])
+@pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("batch,k,classes", [(3, 12, 64), (4, 2049, 7), (5, 20000, 10)])
+def test_head_gradients_over_inputs(batch, k, classes, dtype, over):
+    print(f"head {over} {batch} {k} {classes}", flush=True)
+    plan = _plan(batch, k, dtype)
+    rng = np.random.default_rng(k + 1)
+    tdt = torch.bfloat16 if dtype == BF16 else torch.float32
+    y = torch.from_numpy(rng.standard_normal((batch, 1, 1, k), dtype=np.float32)).cuda().to(tdt)
+    fw = (rng.standard_normal((classes, k)) / np.sqrt(k)).astype(np.float32)
+    fb = rng.standard_normal(classes).astype(np.float32)
+    lab = rng.integers(0, classes, batch).astype(np.int32)
+    yn = y.float().cpu().numpy()
+
+    def dev(a):
+        return torch.from_numpy(a).cuda()
+    fcw = dev(fw)
+    logits, loss = torch.empty((batch, classes), device="cuda"), torch.empty(4, device="cuda")
+    dfb = torch.empty(classes, device="cuda")
+    dy = y if over == "dy_over_y" else torch.empty_like(y)
+    dfw = fcw if over == "d_fc_w_over_fc_w" else torch.empty_like(fcw)
+    ws = torch.empty(L.lrcnn_head_workspace_bytes(plan, classes), dtype=torch.uint8, device="cuda")
+    L.lrcnn_head_loss(plan, y, fcw, dev(fb), dev(lab), logits, loss, dy, dfw, dfb, ws)
+    torch.cuda.synchronize()
+    rl = OH.head_forward(yn, fw, fb)
+    rloss, dlog = OH.softmax_xent(rl, lab)
+    rdy, rdfw, rdfb = OH.head_backward(yn, fw, dlog)
+
+    def rel(a, r):
+        return float(np.abs(a.float().cpu().numpy() - r).max() / np.abs(r).max())
+    # (the bounds of test_head_edges; with dy over y, d_fc_w has no y left)
+    assert rel(logits, rl) < 1e-5
+    assert abs(loss[0].item() - rloss) <= 1e-5 * max(abs(rloss), 1e-2)
+    assert rel(dfb, rdfb) < 1e-5
+    assert rel(dy, rdy) < (1e-5 if dtype == F32 else 2.0 ** -8)
+    if over != "dy_over_y":
+        assert rel(dfw, rdfw) < 1e-5
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
