@@ -51,10 +51,12 @@ void lrcnn_debug_serial_wgrad(int on);
 int lrcnn_debug_fork_wgrad(int mode);
 
 /* On the calling thread, the input gradient of a strided convolution
- * (stride s in both directions) is computed as s^2 launches, one per phase
- * of producer rows and columns ((y + pad) mod s), each with only the taps
- * that reach it: mode 0 = when estimated faster than one launch over all
- * taps (default), 1 = always, 2 = never. Results agree to rounding. */
+ * (stride s in both directions) is computed by the s^2 phases of producer
+ * rows and columns ((y + pad) mod s), each with only the taps that reach it:
+ * mode 0 = when estimated faster than all taps everywhere (default), 1 =
+ * always, 2 = never, 3 = always, each phase in a launch of its own, 4 =
+ * always, all phases in one launch where there is one (stride 2, 16-byte
+ * loads; else as 3). Results agree to rounding. */
 void lrcnn_debug_dgrad_phases(int mode);
 
 /* on != 0: clear and start timing every matrix-core kernel launch

@@ -10,7 +10,8 @@
 namespace lrcnn {
 
 // input gradients of strided convolutions: 0 = by estimate, 1 = always
-// stride phases, 2 = never (kernels.hip)
+// stride phases, 2 = never, 3 = always, each in a launch of its own, 4 =
+// always, in one launch where there is one (kernels.hip)
 extern thread_local int g_phases;
 
 // ------------------------------------------- conv forward / input grad
@@ -1358,7 +1359,8 @@ static int conv_dispatch(const ConvArgs &a, hipStream_t s) {
                       (double)it / 256.0 * c.step_us * c.share) + c.fixed_us;
     };
     const double m128 = est(it128, 128), m64 = est(it64, 64);
-    if (std::min(m128, m64) < ph && (std::min(m128, m64) < one || g_phases == 1)) {
+    const double m = std::min(m128, m64);
+    if (g_phases == 4 || (g_phases != 3 && m < ph && (m < one || g_phases == 1))) {
       const int bm = m64 < m128 ? 64 : 128;
       b.merged = 1;
       b.pst = 2;
@@ -1369,7 +1371,7 @@ static int conv_dispatch(const ConvArgs &a, hipStream_t s) {
       int pr = -1;
       if (prof::on)
         pr = prof::begin(std::string("conv_gemm_kernel<") + (sizeof(T) == 4 ? "float" : "bf16") +
-                             ", 64, dgrad, vec>", fl, s,
+                             ", 64, dgrad, phases>", fl, s,
                          conv_bytes<T, DGRAD>(a, M, 1, false), es);
       if (bm == 64)
         launch_timed(conv_gemm_kernel<T, 64, LRCNN_CONV_KR, DGRAD, true, true, false, 64>, grid, s,
@@ -1379,7 +1381,7 @@ static int conv_dispatch(const ConvArgs &a, hipStream_t s) {
       return (int)hipGetLastError();
     }
   }
-  if (ph >= one && g_phases != 1) return conv_launch<T, DGRAD>(a, s);
+  if (ph >= one && g_phases == 0) return conv_launch<T, DGRAD>(a, s);
   for (int ry = 0; ry < a.sh; ++ry)
     for (int rx = 0; rx < a.sw; ++rx) {
       const PhaseDim py = phase_dim(a.y0, a.y1, a.ph, a.kh, a.sh, ry);

@@ -118,7 +118,7 @@ int profile_entry(int i, const char **name, int64_t *launches, double *ms, doubl
   return 0;
 }
 
-thread_local int g_phases = 0;  // 0: by estimate, 1: always, 2: never
+thread_local int g_phases = 0;  // 0: by estimate (kconv.hpp: the others)
 void set_dgrad_phases(int mode) { g_phases = mode; }
 
 int launch_conv(int dt, int dgrad, const ConvArgs &a, void *stream) {

@@ -144,7 +144,8 @@ struct ConvArgs {
 };
 int launch_conv(int dt, int dgrad, const ConvArgs &a, void *stream);
 // input gradients of strided convolutions on the calling thread: 0 = split
-// into stride phases when estimated faster, 1 = always, 2 = never
+// into stride phases when estimated faster, 1 = always, 2 = never, 3 = always,
+// each in a launch of its own, 4 = always, in one launch where there is one
 void set_dgrad_phases(int mode);
 
 // Split-K selection. A launch of `tiles` output tiles whose K loop has KT
@@ -242,10 +243,6 @@ inline bool split_fits(long long splits, long long M, long long N, const void *p
   if (M * N >= (1ll << 32)) return false;
   return (unsigned long long)splits * (unsigned long long)M * (unsigned long long)N * 4ull <=
          (unsigned long long)part_bytes;
-}
-inline int split_count(long long tiles, int KT, long long part_elems, size_t cap,
-                       const SplitCost &c) {
-  return split_choice(tiles, KT, part_elems, cap, c).s;
 }
 // Tile width and split count of a convolution launch (forward or input
 // gradient, M x N outputs, KT K iterations): 128-row tiles, 64 or 128

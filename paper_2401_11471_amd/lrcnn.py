@@ -354,7 +354,8 @@ def lrcnn_debug_act_fusion(on):
 
 
 def lrcnn_debug_dgrad_phases(mode):
-    """Test hook: strided input gradients by phase (0 estimate, 1 always, 2 never)."""
+    """Test hook: strided input gradients by phase (0 estimate, 1 always, 2 never,
+    3 always in separate launches, 4 always in one launch where there is one)."""
     LIB.lrcnn_debug_dgrad_phases(int(mode))
 
 

@@ -1,7 +1,8 @@
 """Input gradient of strided convolutions split into stride phases (producer
-rows and columns grouped by (y + pad) mod s, each phase a dense launch with
-only the taps that reach it) against the single launch over all taps, and
-both against the float64 oracle. Odd map sizes give phases of unequal
+rows and columns grouped by (y + pad) mod s, each phase dense with only the
+taps that reach it), all in one launch, in launches of their own, and by
+estimate, against the single launch over all taps, and against the float64
+oracle. Odd map sizes give phases of unequal
 size; a 1x1 stride-2 convolution has phases without taps."""
 import numpy as np
 import pytest
@@ -53,14 +54,15 @@ def test_phased_input_gradient(name, net, dt, b, h, w, kw):
     print(f"dgrad phases {name}", flush=True)
     nodes = net()
     inp = Inputs(nodes, b, h, w, 3, dt, seed=21)
-    ph = _run(nodes, inp, 1, want_dx=True, **kw)
     one = _run(nodes, inp, 2, want_dx=True, **kw)
-    # the forward is untouched; the backward agrees with the single launch
-    # to rounding (split-K groupings may differ)
-    assert np.array_equal(ph["y"], one["y"])
-    tol = 2e-2 if dt == BF16 else 1e-5
-    assert rel(ph["dx"], one["dx"]) < tol
-    for v, (p, q) in enumerate(zip(ph["dw"], one["dw"])):
-        if p is not None:
-            assert rel(p, q) < tol, v
-    assert_parity(nodes, inp, ph)
+    for mode in (1, 3, 4):
+        ph = _run(nodes, inp, mode, want_dx=True, **kw)
+        # the forward is untouched; the backward agrees with the single launch
+        # to rounding (split-K groupings may differ)
+        assert np.array_equal(ph["y"], one["y"])
+        tol = 2e-2 if dt == BF16 else 1e-5
+        assert rel(ph["dx"], one["dx"]) < tol, mode
+        for v, (p, q) in enumerate(zip(ph["dw"], one["dw"])):
+            if p is not None:
+                assert rel(p, q) < tol, (mode, v)
+        assert_parity(nodes, inp, ph)
