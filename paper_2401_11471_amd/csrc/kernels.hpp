@@ -175,7 +175,11 @@ void set_dgrad_phases(int mode);
 #define LRCNN_STEP_N128 1.35  // one K iteration of a lone 128 x 128 tile (fp32)
 #endif
 #ifndef LRCNN_NARROW_GAIN
-#define LRCNN_NARROW_GAIN 1.5  // narrow tiles are taken unless wide ones are 1.5x faster
+// Narrow tiles are taken unless wide ones are estimated 1.5x faster. In float32,
+// 1.5 against 1.0: VGG-16 at 1200 x 1800 in 16 bands 218.8 and 221.8 ms per
+// step, layer-wise 157.5 and 149.8; at 224 pixels layer-wise 8.34 and 8.50;
+// ResNet-50 at 600 x 900 layer-wise 9.95 and 10.15; their banded steps equal.
+#define LRCNN_NARROW_GAIN 1.5
 #endif
 // 16-byte vectors per K iteration of a convolution launch: LRCNN_CONV_KR
 // (4 or 8), and LRCNN_CONV_KR_WIN for the bfloat16 forward of windowed
@@ -430,7 +434,11 @@ inline WgradTiles wgrad_tiles(int Co, long long N, long long K, size_t cap, int 
                                         SplitCost{f, 3, 12.0, LRCNN_WG_MAXS, LRCNN_WG_SHARE});
   // float32: 64 rows where the 128-row grid leaves over a quarter of its last
   // round of CUs idle (alone, 512 x 4608 over 6272 pixels: 288 workgroups 448
-  // us, 64 rows 369; 256 x 2304 over 34200, 252 workgroups: 399 and 403)
+  // us, 64 rows 369; 256 x 2304 over 34200, 252 workgroups: 399 and 403). A
+  // layer's weight gradient and recomputed forward together, 128 rows only and
+  // by this rule, us: 512 x 4608 over 1568 pixels 224 and 203, 2240 278 and 246, 9000 1087 and 924; 512 x 2304 over
+  // 6272 359 and 325; 256 x 2304 over 25088 608 and 588; 384 x 1728 over 4620
+  // 148 and 146; none of 16 shapes down to 2048 x 512 over 392 (46, 45) slower
   const long long g128 = ((Co + 127) / 128) * nt * r128.s;
   const bool even = 4 * g128 >= 3 * 256 * ((g128 + 255) / 256);
   if (LRCNN_WG_NARROW && (es == 2 || !even) && r64.us < r128.us) return WgradTiles{64, r64.s};
