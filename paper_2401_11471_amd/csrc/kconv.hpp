@@ -18,9 +18,11 @@ extern thread_local int g_phases;
 // ONE: a single tap (1x1 kernel, or a phase with one tap): each A row's
 // validity and address are fixed for the launch, so a K step only adds the
 // channel offset.
-// BMT: pixels of a tile (64 or 128).
+// BMT: pixels of a tile (64 or 128). C3: a tap-packed float32 forward over
+// exactly 3 channels (a kernel of its own: the choice inside the loop cost
+// maps of 1, 2 and 5 to 7 channels 2-4%).
 template <typename T, int BN, int KR, bool DGRAD, bool VEC, bool S1, bool ONE = false,
-          int BMT = 128>
+          int BMT = 128, bool C3 = false>
 // bfloat16: three workgroups per CU (the register budget is set for it;
 // the swizzled LDS tiles fit three); float32 keeps the registers of two
 __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(ConvArgs a) {
@@ -279,14 +281,14 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 3 : 2) void conv_gemm_kernel(
         const int sy = by[i] + (int)ti_, sx = bx[i] + (int)tj_;
         const bool ok = tok & am[i] & (sx >= 0) & (sy >= a.sy0) & (sy < a.sy1) & (sx < a.Ws);
         const long long off = rbase[i] + (long long)ti_ * srow + (long long)tj_ * a.src.C;
-        if (sizeof(T) == 4 && a.KC == 3) ra[i] = load12(src + off, ok);
+        if constexpr (C3) ra[i] = load12(src + off, ok);
         else ra[i] = load16<T, false>(ok ? src + off : src, ok, a.KC);
       }
 #pragma unroll
       for (int j = 0; j < NBL; ++j) {
         const bool ok = bvld[j] & tok;
         const long long off = bbase[j] - kv * E + (long long)tp * a.KC;
-        if (sizeof(T) == 4 && a.KC == 3) rb[j] = load12(w + off, ok);
+        if constexpr (C3) rb[j] = load12(w + off, ok);
         else rb[j] = load16<T, false>(ok ? w + off : w, ok, a.KC);
       }
       ++kpk;
@@ -1245,6 +1247,17 @@ static int conv_launch(const ConvArgs &a0, hipStream_t s) {
                      s, pr, a);
       else
         launch_timed(conv_gemm_kernel<T, 64, LRCNN_CONV_KR_WIN, false, true, true>, grid, s, pr, a);
+      done = true;
+    }
+  }
+  if constexpr (!DGRAD && sizeof(T) == 4) {
+    if (a.tpack && a.KC == 3) {
+      if (bn == 64)
+        launch_timed(conv_gemm_kernel<T, 64, KR, false, false, true, false, 128, true>, grid, s, pr,
+                     a);
+      else
+        launch_timed(conv_gemm_kernel<T, 128, KR, false, false, true, false, 128, true>, grid, s,
+                     pr, a);
       done = true;
     }
   }
