@@ -44,7 +44,7 @@ void lrcnn_debug_fp_pipeline(int on);
 void lrcnn_debug_serial_wgrad(int on);
 
 /* On the calling thread, the weight gradients that the backward puts on the
- * side stream: mode 0 = by estimate, all of them where the caller's stream is
+ * side stream: mode 0 = by estimate, other ones where the caller's stream is
  * being captured in a graph (default), 1 = all, 2 = every other one. Returns
  * how many the thread's calls put there since the last call of this function.
  * Results are bitwise equal. */

@@ -125,7 +125,7 @@ struct Run {
   std::vector<View> dinit_cv;
   std::vector<int> dinit_t;
   hipStream_t side = nullptr;  // weight-gradient stream (backward only)
-  bool fork_all = false;       // every weight gradient goes there (captured)
+  bool captured = false;       // the caller's stream is being captured
   int n_wg = 0;                // weight gradients so far
   bool wg_pending = false;     // a weight gradient on `side` not yet joined
   bool dx_f32 = false;         // store dL/dx as float32 (a checkpoint's error)
@@ -763,7 +763,7 @@ struct Run {
 
   void use_side(const Plan &p) {
     side = (hipStream_t)p.side_stream;
-    fork_all = capturing(stream);
+    captured = capturing(stream);
   }
 
   // Whether conv v's weight gradient over rows [a, b) goes to the side
@@ -774,21 +774,29 @@ struct Run {
   // ResNet-50 16.4 -> 13.6 ms, block 2 at 28 x 28 layer-wise 160 -> 133 us, the
   // tiny net 692 -> 533 us, ResNet-50's first block at 600 x 900 16.9 -> 15.7
   // ms, block 3 14.3 -> 13.1. From 40 us on the overlap of VGG-16 and block 4
-  // is lost as well. In a replayed graph a fork and join cost less, so all are
-  // forked where the stream is being captured (by the rule -> all): 224-pixel
-  // ResNet-50 12.18 -> 11.56 ms, 2400 x 3600 206.3 -> 203.8, VGG-16 at 224
-  // pixels 12.47 -> 12.49.
+  // is lost as well.
+  // In a replayed graph a fork and join cost less, so where the stream is being
+  // captured all are forked (by the rule above -> all): 224-pixel ResNet-50
+  // 12.18 -> 11.56 ms, 2400 x 3600 206.3 -> 203.8, float32 ResNet-50 at 600 x
+  // 900 28.7 -> 26.4. Except in float32 from 120 us on: such a launch fills the
+  // matrix cores, and in a graph the two kernels of a pair then only slow each
+  // other. VGG-16, all forked -> by this rule (none): 1200 x 1800 in 16 bands
+  // 233.4 -> 220.0 (220.3) ms, 32 images at 224 pixels 41.1 -> 39.7 (39.7), 16
+  // images 22.0 -> 21.7 (21.8), 8 images in 2 bands 10.22 -> 9.91 (9.95), in 4
+  // 11.98 -> 12.01 (12.39). With 60, 200 and 300 us instead of 120: 12.23, 11.98,
+  // 11.97 for those 4 bands, 9.97, 10.17, 10.22 for the 2, and 58.8, 58.5, 60.3
+  // (120: 58.5) at 600 x 900.
   bool fork_wgrad(int v, int a, int b, bool dgrad) {
     ++n_wg;
     if (g_fork_mode) return g_fork_mode == 1 || n_wg % 2 == 0;
-    if (fork_all) return true;
-    if (!dgrad) return false;
     const lrcnn_node &d = P.nodes[v];
     const Shape &sv = P.shp[v], &su = P.shp[d.in0];
     const double px = (double)P.cfg.batch * (b - a) * sv.w;
     const double flops = 2.0 * px * sv.c * d.kh * d.kw * su.c;
     const double bytes = px * (sv.c + (double)d.sh * d.sw * su.c) * P.es;
-    return std::max(flops / (P.es == 2 ? 400e6 : 90e6), bytes / 4e6) >= 10.0;
+    const double us = std::max(flops / (P.es == 2 ? 400e6 : 90e6), bytes / 4e6);
+    if (captured) return P.es == 2 || us < 120.0;
+    return dgrad && us >= 10.0;
   }
 
   // a conv whose error operand the add's backward writes (no error window)

@@ -341,9 +341,9 @@ def lrcnn_debug_serial_wgrad(on):
 
 
 def lrcnn_debug_fork_wgrad(mode):
-    """Test hook: weight gradients on the side stream (0 by estimate, or all of
-    them in a captured graph; 1 all, 2 every other one). Returns how many went
-    there since the last call."""
+    """Test hook: weight gradients on the side stream (0 by estimate, other ones
+    in a captured graph; 1 all, 2 every other one). Returns how many went there
+    since the last call."""
     return LIB.lrcnn_debug_fork_wgrad(int(mode))
 
 

@@ -62,7 +62,7 @@ def test_graph_replay_matches_eager(net, dtype, mode, nb, refine):
     with torch.cuda.graph(graph):
         step()
     torch.cuda.synchronize()
-    # a captured step puts every weight gradient on the side stream
+    # a captured step puts these small weight gradients on the side stream
     assert L.lrcnn_debug_fork_wgrad(0) > nb * refine
 
     for rep in range(3):
