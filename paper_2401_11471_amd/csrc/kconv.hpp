@@ -881,7 +881,8 @@ static double conv_bytes(const ConvArgs &a, long long M, int splits, bool epi) {
 // window that leaves the image, or whose dwords could leave the tensor, its
 // vectors are gathered element by element.
 // A residual add that the planner gives this layer (two branches of a
-// few-channel map and their sum) is computed in the 16-byte store loop.
+// few-channel map and their sum) is computed in the 16-byte store loop (RES, an
+// instantiation of its own: asked per store it cost the others 0.1-0.5%).
 // Where rows and strides keep the parity of every window's first element
 // (ALN: W * C and the horizontal stride times C even), the packing starts at
 // the aligned element, one before the row's first if that is odd (lead, a
@@ -933,7 +934,7 @@ __device__ __forceinline__ RawVec first_elems(const bf16 *p, int lo, int hi) {
 __device__ __host__ static inline int first_lead(bool aln, int pw, int kc) {
   return aln ? (pw * kc) & 1 : 0;
 }
-template <int MI, bool ALN>
+template <int MI, bool ALN, bool RES>
 __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tiles, int KP) {
   // KP: K padded to whole 16-element slices; weight rows have a pitch of an
   // odd number of 16-byte vectors (16 rows of a read on distinct banks)
@@ -1096,7 +1097,7 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(ConvArgs a, int tile
           fdiv_qr((uint32_t)m, a.fw, t_, x_);
           fdiv_qr(t_, a.fr, b_, y_);
           const int y = a.y0 + (int)y_;
-          if (a.res.p) {
+          if constexpr (RES) {
             // fused residual add on the value as stored, then the add's ReLU
             union {
               uint4 u;
@@ -1172,8 +1173,13 @@ static int conv_first_launch(ConvArgs a, int M, hipStream_t s) {
   const bool aln = a.src.W * a.src.C % 2 == 0 && a.sw * a.KC % 2 == 0 && a.src.C == a.KC &&
                    a.kw * a.KC + first_lead(true, a.pw, a.KC) <=
                        8 * conv_row_vecs(a.kw, a.KC, 2);
-  if (wide) aln ? go(conv_first_kernel<2, true>) : go(conv_first_kernel<2, false>);
-  else aln ? go(conv_first_kernel<1, true>) : go(conv_first_kernel<1, false>);
+  auto pick = [&](auto RS) {
+    constexpr bool R = decltype(RS)::value;
+    if (wide) aln ? go(conv_first_kernel<2, true, R>) : go(conv_first_kernel<2, false, R>);
+    else aln ? go(conv_first_kernel<1, true, R>) : go(conv_first_kernel<1, false, R>);
+  };
+  if (a.res.p) pick(std::true_type());
+  else pick(std::false_type());
   return (int)hipGetLastError();
 }
 
